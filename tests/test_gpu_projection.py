@@ -50,6 +50,23 @@ def test_projection_shapes(K, m, n, k):
     _check(_run(K, a, w), a, w, None, None, k)
 
 
+# Tile sizes and the lengths of their K pipelines: 64-wide tiles with 1 to 6
+# slices of 128 (the last one half empty for odd k / 64), 128-wide tiles with
+# 1 to 7 slices of 64, 256-wide tiles with 3 to 6, and launches that mix two
+# sizes (rows past the last full large tile).
+@pytest.mark.parametrize("m,n,k", [(150, 1032, 64), (150, 1032, 128), (65, 72, 192), (150, 1032, 320), (63, 1032, 448),
+                                   (150, 1032, 576), (64, 64, 704), (2050, 2056, 64), (2050, 2056, 128),
+                                   (2047, 2056, 192), (2050, 2056, 320), (2050, 2056, 448), (700, 6144, 256),
+                                   (4112, 4104, 192), (4112, 4096, 256), (4090, 4096, 320), (4112, 4096, 384)])
+def test_projection_tiles(K, m, n, k):
+    rng = np.random.default_rng(m + 3 * n + k)
+    a, w = _bf(rng, (m + 3, k)), _bf(rng, (n, k), 0.05)
+    rows = rng.integers(0, m + 3, m)
+    rows[m // 2] = -1
+    res = _bf(rng, (m, n))
+    _check(_run(K, a, w, rows=rows, res=res, in_place=True), a, w, rows, res, k)
+
+
 def test_projection_small_integers_bit_exact(K):
     # products and float32 sums exact: one rounding to bf16, as the oracle
     rng = np.random.default_rng(40)
