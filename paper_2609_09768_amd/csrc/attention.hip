@@ -8,10 +8,14 @@
 //
 // A dense contraction, so it runs on the matrix cores:
 // v_mfma_f32_32x32x16_bf16 (32x32 tile, K = 16, 8 bf16 per lane).
-// - A workgroup (8 waves, two per SIMD) owns 32*8/hpw selected queries x
-//   hpw query heads of one kv head (hpw = 4 for Llama's G = 4), so all
-//   eight waves share every K/V tile staged in LDS.  Each wave owns 32
-//   queries of one head.
+// - Each wave owns a unit: 32 selected queries of one query head.  The units
+//   of a kv head are numbered queries first, heads second (unit = 32-query
+//   group x G + head of the group), and a workgroup (8 waves, two per SIMD)
+//   takes eight consecutive ones, which share every K/V tile staged in LDS.
+//   So a workgroup spans about 8 / G groups of 32 queries for any G.  (With
+//   odd G it used to take eight units of one head, 256 queries, whose keys
+//   end at more different places: 6,128 rows of 28 / 4 heads recomputed in
+//   full took 2 % longer.)
 // - Scores are computed transposed, S^T = K Q^T: in the accumulator each
 //   lane holds one query and 16 keys, so the softmax max/sum are in-lane
 //   plus one exchange with lane^32.
@@ -39,18 +43,26 @@
 //   the LDS reads of a later operand and three VALU instructions, fenced so
 //   the compiler keeps the interleave and both pipes stay fed.
 // - Key tiles entirely below the smallest position of a wave skip the mask.
+// - A launch costs about 10 us before and after its key tiles (1.1 us each
+//   with most CUs idle, 1.8 us with all busy on random data, at the power
+//   limit): the queries, the largest position (which every wave finds for
+//   itself) and the first three key tiles are requested without a barrier
+//   between them, and tile 0 is used while tiles 1 and 2 arrive: 1,088 rows
+//   of 8 / 2 heads in eight splits 16.8 -> 14.9 us, 4,096 rows of 32 / 8
+//   heads in three 45.5 -> 43.0 us.
 // - Workgroups run longest query block first, and consecutive workgroup
 //   ids (which the dispatcher spreads over the 8 XCDs) take consecutive kv
 //   heads, so with 8 kv heads each XCD's L2 serves one head's K/V.
 // - A selection too small for two workgroups per CU can split every query
 //   block's key tiles over several workgroups (when the caller provides the
 //   workspace for their float32 partial outputs and LSEs); a second kernel
-//   merges the partials of each query head in split order.
+//   merges the partials of each unit in split order.
 
 #include "kvc_internal.h"
 
 #include <limits.h>
 
+#include <algorithm>
 #include <type_traits>
 
 namespace kvc {
@@ -72,14 +84,14 @@ constexpr int kKGroup = 4 * kHeadDim + 32;    // bf16 per four K rows in LDS (10
 constexpr int kKSlot = (kBN / 4) * kKGroup;   // bf16 per K tile
 constexpr int kVSlot = kBN * kHeadDim;        // bf16 per V tile (rows 256 B apart)
 // s_waitcnt immediates (gfx9 encoding: vmcnt bits 3:0 and 15:14, expcnt
-// 6:4, lgkmcnt 11:8): vector-memory count at most 4 or 0, LDS count 0.
+// 6:4, lgkmcnt 11:8): vector-memory count at most 8 or 4, LDS count 0.
 // the four tile-load instructions of a step go after these MFMAs (bit i:
 // MFMA i) of phase 1, then of phase 2 (after every fourth MFMA of phase 1
 // measured best)
 constexpr unsigned kLoadMask1 = 0x8888u;
 constexpr unsigned kLoadMask2 = 0x0000u;
+constexpr int kWaitVm8 = 8 | (7 << 4);
 constexpr int kWaitVm4 = 4 | (7 << 4);
-constexpr int kWaitVm0 = 0 | (7 << 4);
 constexpr float kSumLimit = 65536.0f;     // bound on a lane's tile sum of weights (32 of them)
 
 struct AttnParams {
@@ -94,20 +106,29 @@ struct AttnParams {
   int n_q_heads;
   int n_kv_heads;
   int group;      // G = Hq / Hkv
-  int hpw;        // query heads per workgroup (4, 2 or 1)
-  int qpw;        // queries per workgroup = 32 * kWaves / hpw
-  int n_hgroups;  // G / hpw
-  int n_qblocks;
+  int n_subs;     // groups of 32 queries
+  int n_blocks;   // workgroups' worth of units per kv head
   float scale_log2;  // softmax scale * log2(e)
   uint16_t* out;
   float* lse;
-  // split of each query block's key tiles over n_split workgroups: with
-  // n_split > 1 every workgroup writes its normalised partial output and
-  // its log2-domain LSE here, and attn_combine_kernel merges them
+  // split of each block's key tiles over n_split workgroups: with
+  // n_split > 1 every workgroup writes its normalised partial outputs and
+  // its log2-domain LSEs here, and attn_combine_kernel merges them
   int n_split;
-  float* part_o;    // [n_split][n_sel][Hq][D]
-  float* part_lse;  // [n_split][n_sel][Hq]
+  float* part_o;    // [n_split][kv head][n_sel x G pairs][D], see first_pair
+  float* part_lse;  // [n_split][kv head][n_sel x G pairs]
 };
+
+// Query-head pairs of a kv head before unit u: 32 for a unit, fewer for the
+// units of the last, incomplete group of queries.  The partials of a unit of
+// c queries start there and are stored in the order of the registers that
+// hold them, 16 x [half][query] pieces of 4 channels, so that both kernels
+// move whole lines.
+__device__ __forceinline__ long long first_pair(const AttnParams& P, int u) {
+  const int last = (P.n_subs - 1) * P.group;  // first unit of the last group
+  const int r = (int)(P.n_sel - 32ll * (P.n_subs - 1));
+  return 32ll * min(u, last) + (long long)r * max(u - last, 0);
+}
 
 __device__ __forceinline__ bf16x8 as_bf16x8(const uint4& u) {
   return __builtin_bit_cast(bf16x8, u);
@@ -125,7 +146,6 @@ __global__ __launch_bounds__(kThreads) void sparse_attn_kernel(const AttnParams 
   __shared__ __attribute__((aligned(16))) uint16_t V0[kVSlot], V1[kVSlot], V2[kVSlot], V3[kVSlot];
   uint16_t* const Ks[kSlots] = {K0, K1, K2, K3};
   uint16_t* const Vs[kSlots] = {V0, V1, V2, V3};
-  __shared__ int s_pmax;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -134,32 +154,17 @@ __global__ __launch_bounds__(kThreads) void sparse_attn_kernel(const AttnParams 
   const int ql = lane & 31;
   const int half = lane >> 5;
 
-  const int hk_total = P.n_kv_heads * P.n_hgroups;
-  const int hk = (int)(blockIdx.x % (unsigned)hk_total);
-  const unsigned rest = blockIdx.x / (unsigned)hk_total;
+  const int g = (int)(blockIdx.x % (unsigned)P.n_kv_heads);
+  const unsigned rest = blockIdx.x / (unsigned)P.n_kv_heads;
   const int split = (int)(rest % (unsigned)P.n_split);
-  const int qb = P.n_qblocks - 1 - (int)(rest / (unsigned)P.n_split);
-  const int g = hk % P.n_kv_heads;
-  const int hgroup = hk / P.n_kv_heads;
-  const int hw = wave % P.hpw;
-  const int qs = wave / P.hpw;
-  const int h = g * P.group + hgroup * P.hpw + hw;
-  const long long q0 = (long long)qb * P.qpw;
+  const int block = P.n_blocks - 1 - (int)(rest / (unsigned)P.n_split);
   const long long n_kv = P.n_kv;
 
-  if (tid == 0) s_pmax = -1;
-  __syncthreads();
-  if (tid < P.qpw) {
-    const long long qi = q0 + tid;
-    if (qi < P.n_sel) {
-      long long p = P.q_pos[qi];
-      if (p > n_kv - 1) p = n_kv - 1;
-      if (p >= 0) atomicMax(&s_pmax, (int)p);
-    }
-  }
-
-  // this lane's query (one per lane pair l, l^32)
-  const long long qi = q0 + (long long)qs * 32 + ql;
+  // this wave's unit and this lane's query (one per lane pair l, l^32)
+  const int unit = kWaves * block + wave;  // a launch has fewer than 2^23 blocks
+  const int sub = unit / P.group;
+  const int h = g * P.group + unit % P.group;
+  const long long qi = 32ll * sub + ql;
   const bool in_range = qi < P.n_sel;
   int p = -1;
   long long row = -1;
@@ -170,6 +175,23 @@ __global__ __launch_bounds__(kThreads) void sparse_attn_kernel(const AttnParams 
     if (pp > n_kv - 1) pp = n_kv - 1;
     p = (int)(pp < 0 ? -1 : pp);
   }
+  // largest position among the workgroup's queries (every wave for itself: no
+  // barrier before the first loads)
+  int pmax = -1;
+  {
+    const long long q_first = 32ll * (kWaves * block / P.group);
+    const long long q_end = std::min<long long>(32ll * ((kWaves * block + kWaves - 1) / P.group + 1), P.n_sel);
+    for (long long q0 = q_first; q0 < q_end; q0 += 64) {
+      if (q0 + lane < q_end) {
+        long long pp = P.q_pos[q0 + lane];
+        if (pp > n_kv - 1) pp = n_kv - 1;
+        pmax = max(pmax, (int)(pp < 0 ? -1 : pp));
+      }
+    }
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) pmax = max(pmax, __shfl_xor(pmax, m));
+    pmax = __builtin_amdgcn_readfirstlane(pmax);
+  }
   uint4 qraw[8];
 #pragma unroll
   for (int ks = 0; ks < 8; ++ks) qraw[ks] = make_uint4(0, 0, 0, 0);
@@ -178,25 +200,11 @@ __global__ __launch_bounds__(kThreads) void sparse_attn_kernel(const AttnParams 
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) qraw[ks] = *reinterpret_cast<const uint4*>(qp + ks * 16);
   }
-  // Consume the query registers here so the loads complete before the key
-  // loop; otherwise the wait-count pass treats them as possibly in flight in
-  // every iteration and waits for the next tile's prefetch before the MFMAs.
-#pragma unroll
-  for (int ks = 0; ks < 8; ++ks) {
-    uint32_t a = qraw[ks].x, b = qraw[ks].y, c = qraw[ks].z, d = qraw[ks].w;
-    asm volatile("" : "+v"(a), "+v"(b), "+v"(c), "+v"(d));
-    qraw[ks] = make_uint4(a, b, c, d);
-  }
-  bf16x8 qreg[8];
-#pragma unroll
-  for (int ks = 0; ks < 8; ++ks) qreg[ks] = as_bf16x8(qraw[ks]);
   // smallest position among the wave's live queries (tiles at or below it need no mask)
   int pw_min = in_range ? p : INT_MAX;
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) pw_min = min(pw_min, __shfl_xor(pw_min, m));
   pw_min = __builtin_amdgcn_readfirstlane(pw_min);  // equal in every lane: the mask test is scalar
-  __syncthreads();
-  const int pmax = s_pmax;
   // this workgroup's share of the block's key tiles (all of them unless split)
   const int n_all = (pmax + kBN) / kBN;  // pmax = -1 -> 0 tiles
   const int t0 = (int)((long long)n_all * split / P.n_split);
@@ -251,6 +259,24 @@ __global__ __launch_bounds__(kThreads) void sparse_attn_kernel(const AttnParams 
 #pragma unroll
     for (int q = 0; q < 4; ++q) load_part(t, ks_, vs_, q);
   };
+  // The first three tiles' loads go out behind the query loads.
+  if (n_tiles > 0) {
+    load_tile(0, Ks[0], Vs[0]);
+    load_tile(min(1, n_tiles - 1), Ks[1], Vs[1]);
+    load_tile(min(2, n_tiles - 1), Ks[2], Vs[2]);
+  }
+  // Consume the query registers here so the loads complete before the key
+  // loop; otherwise the wait-count pass treats them as possibly in flight in
+  // every iteration and waits for the next tile's prefetch before the MFMAs.
+#pragma unroll
+  for (int ks = 0; ks < 8; ++ks) {
+    uint32_t a = qraw[ks].x, b = qraw[ks].y, c = qraw[ks].z, d = qraw[ks].w;
+    asm volatile("" : "+v"(a), "+v"(b), "+v"(c), "+v"(d));
+    qraw[ks] = make_uint4(a, b, c, d);
+  }
+  bf16x8 qreg[8];
+#pragma unroll
+  for (int ks = 0; ks < 8; ++ks) qreg[ks] = as_bf16x8(qraw[ks]);
   // QK^T operand (A = K rows kb*32 + lane%32, dims 16 ks + 8 half .. +8):
   // the swizzled piece is 2 (ks ^ e1) + (half ^ (lane & 1)), e1 = bit 1 of
   // the lane, so even and odd ks use two bases with immediate offsets.
@@ -519,18 +545,15 @@ __global__ __launch_bounds__(kThreads) void sparse_attn_kernel(const AttnParams 
   using I3 = std::integral_constant<int, 3>;
 
   if (n_tiles > 0) {
-    load_tile(0, Ks[0], Vs[0]);
-    load_tile(min(1, n_tiles - 1), Ks[1], Vs[1]);
-    load_tile(min(2, n_tiles - 1), Ks[2], Vs[2]);
-  }
-  __builtin_amdgcn_s_waitcnt(kWaitVm0);
-  __builtin_amdgcn_s_barrier();
-  if (n_tiles > 0) {
+    __builtin_amdgcn_s_waitcnt(kWaitVm8);  // tile 0
+    __builtin_amdgcn_s_barrier();
     qk(Ks[0], s[0]);
     mask(0, s[0]);
     m_run = tile_max(s[0]);
     m_use = (m_run == -INFINITY) ? 0.f : m_run;
     exp_half(s[0], H0{}, pbl[0], lt[0]);
+    __builtin_amdgcn_s_waitcnt(kWaitVm4);  // tile 1
+    __builtin_amdgcn_s_barrier();
     int t = 0;
     for (; t + 4 < n_tiles; t += 4) {
       step(I0{}, I0{}, t);
@@ -554,15 +577,16 @@ __global__ __launch_bounds__(kThreads) void sparse_attn_kernel(const AttnParams 
   if (!in_range) return;
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
   if (P.n_split > 1) {
-    const long long pi = ((long long)split * P.n_sel + qi) * P.n_q_heads + h;
-    float* po = P.part_o + pi * kHeadDim + half * 4;
+    const long long pair0 = ((long long)split * P.n_kv_heads + g) * P.n_sel * P.group + first_pair(P, unit);
+    const int c = (int)std::min<long long>(32, P.n_sel - 32ll * sub);
+    float4* po = reinterpret_cast<float4*>(P.part_o + pair0 * kHeadDim) + half * c + ql;
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
       for (int rr = 0; rr < 4; ++rr)
-        *reinterpret_cast<float4*>(po + dt * 32 + rr * 8) =
+        po[(dt * 4 + rr) * 2 * c] =
             make_float4(o[dt][rr * 4] * inv, o[dt][rr * 4 + 1] * inv, o[dt][rr * 4 + 2] * inv, o[dt][rr * 4 + 3] * inv);
-    if (half == 0) P.part_lse[pi] = (l_tot > 0.f) ? m_run + log2f(l_tot) : -INFINITY;
+    if (half == 0) P.part_lse[pair0 + ql] = (l_tot > 0.f) ? m_run + log2f(l_tot) : -INFINITY;
     return;
   }
   uint16_t* op = P.out + (qi * P.n_q_heads + h) * (long long)kHeadDim + half * 4;
@@ -578,33 +602,81 @@ __global__ __launch_bounds__(kThreads) void sparse_attn_kernel(const AttnParams 
     P.lse[qi * P.n_q_heads + h] = (l_tot > 0.f) ? (m_run + log2f(l_tot)) * 0.69314718055994531f : -INFINITY;
 }
 
-// Merge of the split partials of one (query, head) pair per wave, two
-// channels per lane: weights 2^(lse_s - max) in split order, so the result
-// is deterministic; a pair with no visible key gets 0 and LSE -inf.
-__global__ __launch_bounds__(256) void attn_combine_kernel(const float* __restrict__ part_o,
-                                                           const float* __restrict__ part_lse, int n_split,
-                                                           long long n_pairs, uint16_t* __restrict__ out,
-                                                           float* __restrict__ lse) {
-  const long long pair = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (pair >= n_pairs) return;
-  const int lane = threadIdx.x & 63;
+// Merge of the split partials of one unit's queries, one wave per 32 channels
+// of a unit, read in the layout they were written in: weights 2^(lse_s - max)
+// in split order, so the result is deterministic; a query with no visible key
+// gets 0 and LSE -inf.  Bound by the partials' bytes (516 per query, head and
+// split, all requested before the first is used): 696 rows x 32 heads in
+// three splits took 12 us with a wave per query and head, 7.6 us now, 18,856
+// x 4 in two splits 27 and 15 us.
+constexpr int kMaxSplit = 8;
+constexpr int kCombineThreads = 256;  // one unit: four waves, 32 channels each
+template <int NS>
+__global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(const AttnParams P) {
+  const int dt = threadIdx.x >> 6, lane = threadIdx.x & 63, ql = lane & 31, half = lane >> 5;
+  const int g = (int)(blockIdx.x % (unsigned)P.n_kv_heads);
+  const int unit = (int)(blockIdx.x / (unsigned)P.n_kv_heads);
+  const int sub = unit / P.group;
+  const int h = g * P.group + unit % P.group;
+  const long long qi = 32ll * sub + ql;
+  if (qi >= P.n_sel) return;
+  const int c = (int)std::min<long long>(32, P.n_sel - 32ll * sub);
+  const long long pairs = P.n_sel * P.n_q_heads;  // of a split
+  const long long pair0 = (long long)g * P.n_sel * P.group + first_pair(P, unit);
+  const float4* po = reinterpret_cast<const float4*>(P.part_o + pair0 * kHeadDim) + half * c + ql + dt * 4 * 2 * c;
+  float l[NS];
+  float4 v[NS][4];
+#pragma unroll
+  for (int sp = 0; sp < NS; ++sp) {
+    l[sp] = P.part_lse[sp * pairs + pair0 + ql];
+#pragma unroll
+    for (int rr = 0; rr < 4; ++rr) v[sp][rr] = po[sp * pairs * (kHeadDim / 4) + rr * 2 * c];
+  }
   float m = -INFINITY;
-  for (int sp = 0; sp < n_split; ++sp) m = fmaxf(m, part_lse[sp * n_pairs + pair]);
-  float a0 = 0.f, a1 = 0.f, wsum = 0.f;
-  if (m > -INFINITY) {
-    for (int sp = 0; sp < n_split; ++sp) {
-      const float l = part_lse[sp * n_pairs + pair];
-      if (l == -INFINITY) continue;
-      const float w = __builtin_amdgcn_exp2f(l - m);
-      const float2 v = *reinterpret_cast<const float2*>(part_o + (sp * n_pairs + pair) * kHeadDim + 2 * lane);
-      wsum += w;
-      a0 = fmaf(w, v.x, a0);
-      a1 = fmaf(w, v.y, a1);
+#pragma unroll
+  for (int sp = 0; sp < NS; ++sp) m = fmaxf(m, l[sp]);
+  float a[16];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) a[e] = 0.f;
+  float wsum = 0.f;
+#pragma unroll
+  for (int sp = 0; sp < NS; ++sp) {
+    if (l[sp] == -INFINITY) continue;
+    const float w = __builtin_amdgcn_exp2f(l[sp] - m);
+    wsum += w;
+#pragma unroll
+    for (int rr = 0; rr < 4; ++rr) {
+      a[rr * 4] = fmaf(w, v[sp][rr].x, a[rr * 4]);
+      a[rr * 4 + 1] = fmaf(w, v[sp][rr].y, a[rr * 4 + 1]);
+      a[rr * 4 + 2] = fmaf(w, v[sp][rr].z, a[rr * 4 + 2]);
+      a[rr * 4 + 3] = fmaf(w, v[sp][rr].w, a[rr * 4 + 3]);
     }
   }
   const float inv = wsum > 0.f ? 1.f / wsum : 0.f;
-  reinterpret_cast<uint32_t*>(out + pair * kHeadDim)[lane] = pack_bf16x2(a0 * inv, a1 * inv);
-  if (lse && lane == 0) lse[pair] = wsum > 0.f ? (m + log2f(wsum)) * 0.69314718055994531f : -INFINITY;
+  uint16_t* op = P.out + (qi * P.n_q_heads + h) * (long long)kHeadDim + half * 4 + dt * 32;
+#pragma unroll
+  for (int rr = 0; rr < 4; ++rr)
+    *reinterpret_cast<uint2*>(op + rr * 8) = make_uint2(pack_bf16x2(a[rr * 4] * inv, a[rr * 4 + 1] * inv),
+                                                        pack_bf16x2(a[rr * 4 + 2] * inv, a[rr * 4 + 3] * inv));
+  if (P.lse && dt == 0 && half == 0)
+    P.lse[qi * P.n_q_heads + h] = wsum > 0.f ? (m + log2f(wsum)) * 0.69314718055994531f : -INFINITY;
+}
+
+hipError_t launch_combine(const AttnParams& P, hipStream_t s) {
+  const dim3 grid((unsigned)(P.n_subs * P.group) * (unsigned)P.n_kv_heads), block(kCombineThreads);
+  switch (P.n_split) {
+#define KVC_COMBINE(NS) case NS: hipLaunchKernelGGL(attn_combine_kernel<NS>, grid, block, 0, s, P); break
+    KVC_COMBINE(2);
+    KVC_COMBINE(3);
+    KVC_COMBINE(4);
+    KVC_COMBINE(5);
+    KVC_COMBINE(6);
+    KVC_COMBINE(7);
+    KVC_COMBINE(8);
+#undef KVC_COMBINE
+  }
+  static_assert(kMaxSplit == 8, "one merge kernel for each number of splits");
+  return hipGetLastError();
 }
 
 // Splitting aims at one workgroup per CU with at least 4 key tiles each
@@ -612,42 +684,39 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float* __restri
 // measured against two per CU and 8 tiles, 4.1k at 15 % takes 56 instead of
 // 76 us, 32k at 5 % 541 instead of 561 us, Tiny 22.6 instead of 25.3 us
 // (more splits cost more partial writes and merging than they balance).
-constexpr int kTargetWorkgroups = 256;
-constexpr int kMaxSplit = 8;
+// Cutting later blocks, which have more keys, into more shares than earlier
+// ones was measured too: 4.1k 12 % faster, but one kv head at 124k 8 % slower
+// (shares of different blocks then start at different keys, and the L2 no
+// longer serves them together).
+constexpr int kCus = 256;
 constexpr int kMinTilesPerSplit = 4;
 
-struct Grid {
-  int hpw, qpw, n_hgroups, n_qblocks;
-  long long n_wg;
-};
-Grid grid_of(int64_t n_sel, int n_q_heads, int n_kv_heads) {
-  Grid g;
+long long div_up(long long a, long long b) { return (a + b - 1) / b; }
+
+// Query blocks the split and the workspace size go by: 64 queries of four
+// heads, 128 of two or 256 of one.
+long long budget_blocks(int64_t n_sel, int n_q_heads, int n_kv_heads) {
   const int group = n_q_heads / n_kv_heads;
-  g.hpw = (group % 4 == 0) ? 4 : (group % 2 == 0) ? 2 : 1;
-  g.qpw = 32 * (kWaves / g.hpw);
-  g.n_hgroups = group / g.hpw;
-  g.n_qblocks = (int)((n_sel + g.qpw - 1) / g.qpw);
-  g.n_wg = (long long)g.n_qblocks * n_kv_heads * g.n_hgroups;
-  return g;
+  const int hpw = (group % 4 == 0) ? 4 : (group % 2 == 0) ? 2 : 1;
+  return div_up(n_sel, 32 * (kWaves / hpw)) * n_kv_heads * (group / hpw);
+}
+
+int attention_splits(int64_t n_sel, int n_q_heads, int n_kv_heads) {
+  if (n_sel <= 0) return 1;
+  const long long n_wg = budget_blocks(n_sel, n_q_heads, n_kv_heads);
+  if (n_wg >= 2 * kCus) return 1;
+  // one to two workgroups per CU: with positions spread over the context
+  // the longest query blocks alone would set the time (about twice the
+  // average load), so halve every block's key range
+  if (n_wg >= kCus) return 2;
+  return (int)std::min<long long>(div_up(kCus, n_wg), kMaxSplit);
 }
 
 }  // namespace
 
-int attention_splits(int64_t n_sel, int n_q_heads, int n_kv_heads) {
-  if (n_sel <= 0) return 1;
-  const Grid g = grid_of(n_sel, n_q_heads, n_kv_heads);
-  if (g.n_wg >= 2 * kTargetWorkgroups) return 1;
-  // one to two workgroups per CU: with positions spread over the context
-  // the longest query blocks alone would set the time (about twice the
-  // average load), so halve every block's key range
-  if (g.n_wg >= kTargetWorkgroups) return 2;
-  const long long s = (kTargetWorkgroups + g.n_wg - 1) / g.n_wg;
-  return (int)(s < kMaxSplit ? s : kMaxSplit);
-}
-
 int64_t attention_work_items(int64_t n_sel, int n_q_heads, int n_kv_heads) {
   if (n_sel <= 0) return 0;
-  return grid_of(n_sel, n_q_heads, n_kv_heads).n_wg * kThreads;
+  return budget_blocks(n_sel, n_q_heads, n_kv_heads) * kThreads;
 }
 
 size_t attention_ws_bytes(int64_t n_sel, int n_q_heads, int n_kv_heads) {
@@ -673,12 +742,9 @@ hipError_t launch_attention(const uint16_t* q, int64_t n_q_rows, const int32_t* 
   P.n_kv = n_kv;
   P.n_q_heads = n_q_heads;
   P.n_kv_heads = n_kv_heads;
-  const Grid g = grid_of(n_sel, n_q_heads, n_kv_heads);
   P.group = n_q_heads / n_kv_heads;
-  P.hpw = g.hpw;
-  P.qpw = g.qpw;
-  P.n_hgroups = g.n_hgroups;
-  P.n_qblocks = g.n_qblocks;
+  P.n_subs = (int)div_up(n_sel, 32);
+  P.n_blocks = (int)div_up((long long)P.n_subs * P.group, kWaves);
   P.scale_log2 = scale * 1.4426950408889634f;
   P.out = out;
   P.lse = lse;
@@ -687,21 +753,17 @@ hipError_t launch_attention(const uint16_t* q, int64_t n_q_rows, const int32_t* 
   int sp = 1;
   const size_t need = attention_ws_bytes(n_sel, n_q_heads, n_kv_heads);
   if (ws && need > 0 && ws_bytes >= need) {
-    const long long tiles = (n_kv + kBN - 1) / kBN;
-    const long long cap = tiles / kMinTilesPerSplit;
-    sp = attention_splits(n_sel, n_q_heads, n_kv_heads);
-    if (sp > cap) sp = (int)(cap > 1 ? cap : 1);
+    const long long cap = div_up(n_kv, kBN) / kMinTilesPerSplit;
+    sp = (int)std::max<long long>(1, std::min<long long>(attention_splits(n_sel, n_q_heads, n_kv_heads), cap));
   }
   P.n_split = sp;
   P.part_o = sp > 1 ? static_cast<float*>(ws) : nullptr;
   P.part_lse = sp > 1 ? P.part_o + (size_t)sp * n_sel * n_q_heads * kHeadDim : nullptr;
-  hipLaunchKernelGGL(sparse_attn_kernel, dim3((unsigned)(g.n_wg * sp)), dim3(kThreads), 0, s, P);
-  hipError_t e = hipGetLastError();
+  hipLaunchKernelGGL(sparse_attn_kernel, dim3((unsigned)P.n_blocks * (unsigned)n_kv_heads * (unsigned)sp),
+                     dim3(kThreads), 0, s, P);
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess || sp == 1) return e;
-  const long long pairs = n_sel * (long long)n_q_heads;
-  hipLaunchKernelGGL(attn_combine_kernel, dim3((unsigned)((pairs + 3) / 4)), dim3(256), 0, s, P.part_o,
-                     P.part_lse, sp, pairs, out, lse);
-  return hipGetLastError();
+  return launch_combine(P, s);
 }
 
 }  // namespace kvc

@@ -98,9 +98,8 @@ hipError_t launch_attention(const uint16_t* q, int64_t n_q_rows, const int32_t* 
                             const uint16_t* v, int64_t n_kv, int n_q_heads, int n_kv_heads,
                             float scale, uint16_t* out, float* lse, void* ws, size_t ws_bytes,
                             hipStream_t s);
-int attention_splits(int64_t n_sel, int n_q_heads, int n_kv_heads);
-// Work-items of the attention launch (and of its merge launch) without a
-// key-range split; a shape above 2^32 - 1 of them cannot be launched.
+// Bound on the work-items of the attention launch without a key-range split;
+// a shape above 2^32 - 1 of them is refused.
 int64_t attention_work_items(int64_t n_sel, int n_q_heads, int n_kv_heads);
 // Decoder-layer steps around the attention (layer_ops.hip).
 hipError_t launch_rms_norm(const uint16_t* x, int64_t n_x_rows, const int32_t* rows, int64_t n,
