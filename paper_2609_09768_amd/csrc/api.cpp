@@ -676,6 +676,90 @@ kvc_status blend_layer(const char* W, const kvc_layout* L, const kvc_plan* plan,
   return ok();
 }
 
+// An allocation of host or device memory that kernels on this device reach.
+struct Allocation {
+  const char* base = nullptr;    // as the caller addresses it
+  size_t size = 0;
+  const char* mapped = nullptr;  // as this device does
+  bool host = false;
+
+  bool holds(const void* p, size_t bytes) const {
+    const char* c = static_cast<const char*>(p);
+    return base && c >= base && bytes <= size && (size_t)(c - base) <= size - bytes;
+  }
+  // Looks up the allocation p lies in; false for anything else (ordinary
+  // host memory, another device's memory).
+  bool find(const void* p, int device) {
+    *this = Allocation();
+    hipPointerAttribute_t a;
+    hipDeviceptr_t b = nullptr;
+    size_t n = 0;
+    if (hipPointerGetAttributes(&a, p) != hipSuccess || (a.type != hipMemoryTypeHost && a.type != hipMemoryTypeDevice) ||
+        a.device != device || !a.devicePointer || hipMemGetAddressRange(&b, &n, const_cast<void*>(p)) != hipSuccess ||
+        static_cast<const char*>(p) < static_cast<const char*>(b)) {
+      (void)hipGetLastError();  // not an error of this call
+      return false;
+    }
+    base = static_cast<const char*>(b);
+    size = n;
+    host = a.type == hipMemoryTypeHost;
+    mapped = static_cast<const char*>(a.devicePointer) - (static_cast<const char*>(p) - base);
+    return true;
+  }
+};
+
+// The copies of the transfer stage on one stream.  A run of chunk caches that
+// a kernel can read (pinned host memory mapped into this GPU, or its own
+// memory) goes into a list copied by one launch unless it is large and in
+// host memory; the rest goes to hipMemcpyAsync, as does whatever does not lie
+// inside one allocation (which that call checks).
+class StageCopies {
+ public:
+  explicit StageCopies(hipStream_t s) : s_(s) { ok_ = hipGetDevice(&dev_) == hipSuccess; }
+
+  // The following copies go to [dst, dst + bytes).
+  void target(const void* dst, size_t bytes) {
+    Allocation d;
+    dst_ok_ = ok_ && d.find(dst, dev_) && !d.host && d.holds(dst, bytes);
+  }
+  hipError_t add(void* dst, const void* src, size_t bytes) {
+    // A DMA copy costs about 9 us beside its bytes, so 1 MB takes it 28 us
+    // and the kernel 20; larger runs leave all CUs to the layer that computes
+    // meanwhile.  Copies inside the device's memory are kernels either way.
+    const void* from = dst_ok_ && (src_.holds(src, bytes) || (src_.find(src, dev_) && src_.holds(src, bytes)))
+                           ? src_.mapped + (static_cast<const char*>(src) - src_.base)
+                           : nullptr;
+    if (from && aligned16(from) && !(src_.host && bytes >= kMinDmaBytes)) {
+      kvc::CopyList& list = src_.host ? host_ : device_;
+      if (kvc::copy_list_add(&list, dst, from, bytes)) return hipSuccess;
+      const hipError_t e = flush(src_.host);
+      if (e != hipSuccess) return e;
+      if (kvc::copy_list_add(&list, dst, from, bytes)) return hipSuccess;
+    }
+    return hipMemcpyAsync(dst, src, bytes, hipMemcpyDefault, s_);
+  }
+  hipError_t finish() {
+    const hipError_t e = flush(true);
+    return e != hipSuccess ? e : flush(false);
+  }
+
+ private:
+  static constexpr size_t kMinDmaBytes = size_t(1) << 20;
+
+  hipError_t flush(bool host) {
+    kvc::CopyList& list = host ? host_ : device_;
+    const hipError_t e = kvc::launch_copy_list(list, host, s_);
+    list.n = 0;
+    return e;
+  }
+
+  hipStream_t s_;
+  int dev_ = -1;
+  bool ok_ = false, dst_ok_ = false;
+  Allocation src_;  // the last source's; serves the following ones of this call
+  kvc::CopyList host_, device_;
+};
+
 }  // namespace
 
 extern "C" {
@@ -914,11 +998,13 @@ kvc_status kvc_stage_layers(const kvc_layout* L, const kvc_plan* plan, int32_t n
   if (st != KVC_OK) return st;
   const hipStream_t s = as_stream(stream);
   const size_t row_bytes = (size_t)L->n_kv_heads * L->head_dim * 2;
+  StageCopies copies(s);
   for (int32_t l = 0; l < n_layers; ++l) {
     // copies, merging chunks whose sources are back to back; K and V apart
     for (int which = 0; which < 2; ++which) {
       const void* const* src = (which == 0 ? k_chunks : v_chunks) + (size_t)l * nc;
       char* dst = static_cast<char*>(which == 0 ? k_cache[l] : v_cache[l]);
+      copies.target(dst, (size_t)li.n_reused * row_bytes);
       const char* run_src = nullptr;
       size_t run_dst = 0, run_bytes = 0, row0 = 0;
       for (size_t i = 0; i <= nc; ++i) {
@@ -931,7 +1017,7 @@ kvc_status kvc_stage_layers(const kvc_layout* L, const kvc_plan* plan, int32_t n
         const bool gap = zero && !c;
         const bool extend = c && run_bytes > 0 && c == run_src + run_bytes && row0 * row_bytes == run_dst + run_bytes;
         if (!extend && (end || gap || c) && run_bytes > 0) {
-          const hipError_t e = hipMemcpyAsync(dst + run_dst, run_src, run_bytes, hipMemcpyDefault, s);
+          const hipError_t e = copies.add(dst + run_dst, run_src, run_bytes);
           if (e != hipSuccess) return hip_fail(W, e);
           run_bytes = 0;
         }
@@ -947,8 +1033,10 @@ kvc_status kvc_stage_layers(const kvc_layout* L, const kvc_plan* plan, int32_t n
         if (!end) row0 += (size_t)L->chunk_len[i];
       }
     }
+    hipError_t e = copies.finish();
+    if (e != hipSuccess) return hip_fail(W, e);
     // zeros for the separator slots, keys adjusted in place
-    hipError_t e = kvc::launch_rope_shift(plan->device, plan->layout_id, L->n_chunks, li.n_tiles, L->n_kv_heads,
+    e = kvc::launch_rope_shift(plan->device, plan->layout_id, L->n_chunks, li.n_tiles, L->n_kv_heads,
                                           static_cast<const uint16_t*>(k_cache[l]),
                                           static_cast<uint16_t*>(k_cache[l]), static_cast<uint16_t*>(v_cache[l]), s);
     if (e != hipSuccess) return hip_fail(W, e);

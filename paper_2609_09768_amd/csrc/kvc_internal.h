@@ -119,6 +119,22 @@ hipError_t launch_gemm(int64_t m, int64_t n, int64_t k, const uint16_t* a, int64
 // Work-items of that launch (HIP allows fewer than 2^32 per launch).
 int64_t gemm_work_items(int64_t m, int64_t n);
 
+// ---- copies of the transfer stage (stage_copy.hip) -----------------------------
+// Copies for one launch, all from host or all from device memory; 16-byte
+// aligned, whole 16-byte units.  A kernel argument, so it stays below 4 KB.
+struct CopyList {
+  static constexpr int kMax = 160;
+  const void* src[kMax];
+  void* dst[kMax];
+  uint32_t units[kMax];     // 16-byte units of each copy
+  uint32_t end_tile[kMax];  // running count of the launch's tiles
+  int n = 0;
+};
+// False when the list is full (or the copy is too large for it).
+bool copy_list_add(CopyList* L, void* dst, const void* src, size_t bytes);
+// host: the sources are in host memory.
+hipError_t launch_copy_list(const CopyList& L, bool host, hipStream_t s);
+
 // ---- static scratch (static_scratch.hip) -------------------------------------
 // Size of the per-GPU device array behind kvc_blend_prefill_layer_noalloc
 // (KVC_STATIC_SCRATCH_BYTES in kvc.h).

@@ -187,3 +187,58 @@ def test_two_stream_pipeline_matches_layer_by_layer(K, name):
         assert np.array_equal(lses[l].cpu().numpy(), ref[l]["lse"]), l
         assert np.array_equal(_val(down_bf16(kcs[l])), _val(ref[l]["k_cache"])), l
         assert np.array_equal(down_bf16(vcs[l]), ref[l]["v_cache"]), l
+
+
+@pytest.mark.parametrize("kind", ["pinned", "device", "mixed"])
+def test_stage_layer_many_fragments(K, kind):
+    """Fragments out of order in one allocation: more than one list of copies,
+    empty chunks, a run above the size left to the copy engines, and (mixed)
+    fragments a kernel cannot take (ordinary memory, odd addresses).  Also
+    replayed from a graph."""
+    rng = np.random.default_rng(11)
+    lens = [int(x) for x in rng.integers(0, 12, 420)] + [2100] + [int(x) for x in rng.integers(1, 40, 30)]
+    w = W.Workload("fragments", tuple(lens), 0, 8, 2)
+    L, plan = _layout_plan(K, w, zero=False)
+    n_r, re = w.n_reused, 2 * 128
+    row0 = np.concatenate([[0], np.cumsum(lens)])
+    k = torch.from_numpy(rng.integers(0, 2 ** 14, (n_r, re)).astype(np.int16))
+    v = torch.from_numpy(rng.integers(0, 2 ** 14, (n_r, re)).astype(np.int16))
+    order = rng.permutation(len(lens))
+    at, ptrs, keep = 0, {}, []
+    for name, src in (("k", k), ("v", v)):
+        arena = torch.zeros(2 * n_r * re + 64 * len(lens), dtype=torch.int16)
+        arena = arena.cuda() if kind == "device" else arena.pin_memory()
+        keep.append(arena)
+        at, ptrs[name] = 0, [None] * len(lens)
+        for i in order:
+            part = src[row0[i]:row0[i + 1]].reshape(-1)
+            if kind == "mixed" and i % 7 == 3:
+                keep.append(part.clone())            # ordinary memory
+                ptrs[name][i] = keep[-1].data_ptr()
+                continue
+            off = at + (1 if kind == "mixed" and i % 5 == 1 else 0)
+            arena[off:off + part.numel()] = part
+            ptrs[name][i] = arena.data_ptr() + 2 * off
+            at = (off + part.numel() + 31) // 8 * 8
+    kc = torch.zeros((n_r, 2, 128), dtype=torch.int16, device="cuda:0")
+    vc = torch.zeros_like(kc)
+    want_k = torch.empty_like(kc)
+    K.kvc_rope_shift(L, plan, k.cuda(), want_k)
+
+    def check():
+        torch.cuda.synchronize()
+        assert torch.equal(vc.cpu().reshape(n_r, re), v)
+        assert torch.equal(kc, want_k)
+
+    K.kvc_stage_layer(L, plan, ptrs["k"], ptrs["v"], kc, vc)
+    check()
+    if kind == "mixed":
+        return
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        K.kvc_stage_layer(L, plan, ptrs["k"], ptrs["v"], kc, vc)
+    for _ in range(3):
+        kc.zero_(), vc.zero_()
+        (torch.randn(1 << 20, device="cuda:0") * 2).sum().item()   # unrelated eager work
+        g.replay()
+        check()
