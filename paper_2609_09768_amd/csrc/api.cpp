@@ -280,12 +280,12 @@ hipError_t shift_and_select(const kvc_layout* L, const LayoutInfo& li, const kvc
     double* dev = static_cast<double*>(ws);
     void* tws = static_cast<char*>(ws) + kvc::align256(sizeof(double) * (size_t)li.n_reused);
     e = kvc::launch_kv_deviation(li.n_reused, hkv, static_cast<const uint16_t*>(k_cache),
-                                 static_cast<const uint16_t*>(k_fresh), dev, s);
+                                 static_cast<const uint16_t*>(k_fresh), dev, tws, kvc::topk_clear_bytes(li.n_reused), s);
     if (e != hipSuccess) return e;
-    return kvc::launch_select_topk(dev, li.n_reused, k, L->n_query, sel, tws, s);
+    return kvc::launch_select_topk(dev, li.n_reused, k, L->n_query, sel, tws, true, s);
   }
   // k == 0: only the query rows; k == n_reused: every row (causal attention)
-  return kvc::launch_select_topk(nullptr, li.n_reused, k, L->n_query, sel, nullptr, s);
+  return kvc::launch_select_topk(nullptr, li.n_reused, k, L->n_query, sel, nullptr, false, s);
 }
 
 }  // namespace
@@ -437,7 +437,7 @@ kvc_status kvc_kv_deviation(int64_t n_rows, int32_t n_kv_heads, int32_t head_dim
   st = need_device(W);
   if (st != KVC_OK) return st;
   hipError_t e = kvc::launch_kv_deviation(n_rows, n_kv_heads, static_cast<const uint16_t*>(k_cached),
-                                          static_cast<const uint16_t*>(k_fresh), dev_out,
+                                          static_cast<const uint16_t*>(k_fresh), dev_out, nullptr, 0,
                                           as_stream(stream));
   if (e != hipSuccess) return hip_fail(W, e);
   return ok();
@@ -470,7 +470,7 @@ static kvc_status select_topk_impl(const char* W, const double* dev, int64_t n, 
   if (st != KVC_OK) return st;
   st = need_device(W);
   if (st != KVC_OK) return st;
-  hipError_t e = kvc::launch_select_topk(dev, n, k, n_append, idx_out, ws, s);
+  hipError_t e = kvc::launch_select_topk(dev, n, k, n_append, idx_out, ws, false, s);
   if (e != hipSuccess) return hip_fail(W, e);
   return ok();
 }

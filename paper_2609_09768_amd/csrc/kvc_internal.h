@@ -64,13 +64,18 @@ struct TopkState {
 };
 constexpr int kTopkRowsPerBlock = 2048;  // 256 threads x 8 rows
 inline int64_t topk_blocks(int64_t n) { return (n + kTopkRowsPerBlock - 1) / kTopkRowsPerBlock; }
-// State of the fused selection (one launch for all passes, grid barriers):
-// three rotating byte histograms and the barrier's arrival counter.
+// State of the fused selection (one launch for all steps, grid barriers),
+// zero at its start: three rotating histograms, the barrier's arrival
+// counter, the range of the keys and the candidates' count.
 struct TopkFused {
   unsigned int hist[3][256];
   unsigned int arrive;
-  unsigned int pad[63];
+  unsigned int cand;
+  unsigned long long max_key;
+  unsigned long long max_not;
+  unsigned int pad[58];
 };
+static_assert(sizeof(TopkFused) == 3 * 1024 + 256, "part of the workspace size");
 inline size_t topk_ws_bytes(int64_t n) {
   const size_t state = sizeof(TopkState) > sizeof(TopkFused) ? sizeof(TopkState) : sizeof(TopkFused);
   return align256(state) + align256(size_t(2) * sizeof(unsigned int) * size_t(topk_blocks(n) > 0 ? topk_blocks(n) : 1));
@@ -82,10 +87,16 @@ inline size_t topk_ws_bytes(int64_t n) {
 hipError_t launch_rope_shift(const void* plan, uint64_t layout_hash, int n_chunks, int n_tiles, int n_kv_heads,
                              const uint16_t* k_src, uint16_t* k_dst, uint16_t* v_zero,
                              hipStream_t s);
+// clear, clear_bytes: memory zeroed by the same launch (16-byte units; the
+// selection's state), or NULL, 0.
 hipError_t launch_kv_deviation(int64_t n_rows, int n_kv_heads, const uint16_t* k_cached,
-                               const uint16_t* k_fresh, double* dev, hipStream_t s);
+                               const uint16_t* k_fresh, double* dev, void* clear, size_t clear_bytes,
+                               hipStream_t s);
+// Bytes at the start of the selection's workspace to be zero when it starts.
+size_t topk_clear_bytes(int64_t n);
+// cleared: they are; otherwise a launch of its own does it.
 hipError_t launch_select_topk(const double* dev, int64_t n, int64_t k, int64_t n_append,
-                              int32_t* idx_out, void* ws, hipStream_t s);
+                              int32_t* idx_out, void* ws, bool cleared, hipStream_t s);
 hipError_t launch_scatter_rows(const int32_t* sel, int64_t n_sel, int compact,
                                const uint16_t* k_fresh, const uint16_t* v_fresh,
                                int64_t n_fresh, uint16_t* k_cache, uint16_t* v_cache,

@@ -5,23 +5,28 @@
 // ties to the lower row, returned in ascending row order.
 //
 // No sort.  Each float64 d maps to a 64-bit key whose unsigned order is the
-// order of d.  A radix select finds the k-th largest key T one byte at a
-// time (8 passes over the keys, most significant byte first): every
-// workgroup histograms the byte of the keys that still match the prefix
-// found so far, and the last workgroup to finish (atomic ticket) picks the
-// byte, updates the prefix and the remaining rank, and clears the
-// histogram for the next pass.  Then rows with key > T, plus the first
-// `rem` rows with key == T in row order, are compacted in row order with
-// a per-block count and a scan; this yields the ascending output
-// directly.  n and k are known on the host, so nothing is read back.
+// order of d, and the k-th largest key is closed in on by histograms.  n and k
+// are known on the host, so nothing is read back, and the output is written
+// in row order directly (per-block or per-thread counts and a scan).
 //
-// From 16,385 to 262,144 candidates the passes, count and write run in one
-// launch with grid barriers (below).  Up to 16,384 candidates (contexts to
-// about 16k tokens) one workgroup does all of it in one launch: each of its 1,024 threads keeps 16 consecutive
-// rows' keys in registers (32 would spill), the 8 passes histogram into
-// per-wave LDS bins, and two block scans write the output.  Small layers
-// would otherwise spend most of their time in the 11 dependent launches of
-// the general path.
+// Up to 262,144 candidates the histograms follow the keys: the first covers
+// [smallest key, largest key] (bins of a power of two in width), the next the
+// bin the threshold fell into, until that bin holds few keys, which are then
+// ranked against each other (by key, then row), or exactly as many as are
+// still to be taken, or only equal keys, which are taken by row.  Deviations
+// of one layer lie within a few octaves, so one histogram (of 2,048 bins) or
+// two (of 256) are enough where digits of the raw key take eight passes; keys
+// from the whole float64 range take up to six or eight.
+// - Up to 16,384 candidates (contexts to about 16k tokens): one workgroup of
+//   1,024 threads, keys in registers, bins in LDS.
+// - Up to 262,144: one launch of a workgroup per 2,048 rows with grid barriers
+//   between the histograms (below).
+// - Above: a radix select one byte at a time (8 passes over the keys, most
+//   significant byte first): every workgroup histograms the byte of the keys
+//   that still match the prefix found so far, and the last workgroup to
+//   finish (atomic ticket) picks the byte, updates the prefix and the
+//   remaining rank, and clears the histogram for the next pass; then a count
+//   and an ordered write, 11 launches.
 #include "kvc_internal.h"
 
 namespace kvc {
@@ -200,12 +205,43 @@ __global__ __launch_bounds__(kThreads) void topk_write(const double* __restrict_
 // ---- single-workgroup path -------------------------------------------------
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallWaves = kSmallThreads / 64;
-constexpr int kSmallItems = 16;  // consecutive rows per thread, keys in registers
+constexpr int kSmallItems = 16;  // consecutive rows per thread at most, keys in registers
 constexpr long long kSmallMax = (long long)kSmallThreads * kSmallItems;
+constexpr int kSmallBins = 2048;
+constexpr int kMaxCand = 128;    // keys left in the threshold's bin that are ranked one against another
 
-// Exclusive scan over the block's 1,024 threads (wave scans + wave totals).
-__device__ __forceinline__ unsigned int scan1024(unsigned int v, unsigned int* wsum,
-                                                 unsigned int& total) {
+// The keys that may still be selected: [lo, lo + 2^bits), and what is known
+// of them.  Uniform over the workgroup (and the grid).
+struct Bracket {
+  unsigned long long lo;
+  int bits;            // 64: everything from lo on
+  long long rem;       // rows of the bracket to take; every key above it is taken
+  unsigned int count;  // keys in the bracket
+  __device__ bool in(unsigned long long key) const { return key >= lo && (bits >= 64 || ((key - lo) >> bits) == 0); }
+  __device__ bool above(unsigned long long key) const { return bits < 64 && key >= lo && ((key - lo) >> bits) != 0; }
+  // how the rest is decided
+  __device__ bool all() const { return (long long)count == rem; }
+  __device__ bool few() const { return count <= kMaxCand; }
+  __device__ bool equal() const { return bits == 0; }
+  __device__ bool done() const { return all() || few() || equal(); }
+};
+
+// Bits of a bracket that spans [lo, hi].
+__device__ __forceinline__ int span_bits(unsigned long long lo, unsigned long long hi) { return 64 - __clzll((long long)(hi - lo)); }
+
+// Largest of two values over a wave.
+__device__ __forceinline__ void wave_max2(unsigned long long& a, unsigned long long& b) {
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) {
+    const unsigned long long x = __shfl_xor(a, m, 64), y = __shfl_xor(b, m, 64);
+    a = x > a ? x : a;
+    b = y > b ? y : b;
+  }
+}
+
+// Exclusive scan over the block's WAVES x 64 threads (wave scans + wave totals).
+template <int WAVES>
+__device__ __forceinline__ unsigned int block_scan(unsigned int v, unsigned int* wsum, unsigned int& total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   unsigned int incl = v;
 #pragma unroll
@@ -217,7 +253,7 @@ __device__ __forceinline__ unsigned int scan1024(unsigned int v, unsigned int* w
   __syncthreads();
   unsigned int before = 0u, tot = 0u;
 #pragma unroll
-  for (int w = 0; w < kSmallWaves; ++w) {
+  for (int w = 0; w < WAVES; ++w) {
     const unsigned int x = wsum[w];
     before += (w < wave) ? x : 0u;
     tot += x;
@@ -227,127 +263,162 @@ __device__ __forceinline__ unsigned int scan1024(unsigned int v, unsigned int* w
   return before + incl - v;
 }
 
+// Rank of a key of the bracket among the candidates (larger first, then lower row).
+__device__ __forceinline__ int rank_of(unsigned long long key, int row, const unsigned long long* ck, const int* cr, int n) {
+  int r = 0;
+  for (int j = 0; j < n; ++j) r += (ck[j] > key) || (ck[j] == key && cr[j] < row);
+  return r;
+}
+
+// One workgroup: 4,000 candidates 22 -> 9 us, 1,024 18 -> 7 us against eight
+// byte passes; bound by the chain of its steps (loads, reduction, histogram,
+// scan, rank, scan, store), 1 to 2 us each.
+template <int ITEMS>
 __global__ __launch_bounds__(kSmallThreads) void topk_small(const double* __restrict__ dev, long long n,
                                                             long long k, long long n_append,
                                                             int32_t* __restrict__ out) {
-  __shared__ unsigned int wh[kSmallWaves][256];  // per-wave byte histograms
-  __shared__ unsigned int cnt[256];
+  __shared__ unsigned int hist[kSmallBins];
   __shared__ unsigned int wsum[kSmallWaves];
-  __shared__ unsigned long long s_prefix, s_mask;
-  __shared__ long long s_rem;
+  __shared__ unsigned long long smax[kSmallWaves], sneg[kSmallWaves];
+  __shared__ unsigned long long ck[kMaxCand];
+  __shared__ int cr[kMaxCand];
+  __shared__ Bracket s_next;
+  __shared__ unsigned int s_cand;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const long long base = (long long)t * kSmallItems;
-  unsigned long long key[kSmallItems];
-#pragma unroll
-  for (int i = 0; i < kSmallItems; ++i) key[i] = (base + i < n) ? order_key(dev[base + i]) : 0ull;
-
-  unsigned long long prefix = 0ull, mask = 0ull;
-  long long rem = k;
-  for (int shift = 56; shift >= 0; shift -= 8) {
-    // a wave's own bins: cleared and filled by that wave alone, in order
-    for (int b = lane; b < 256; b += 64) wh[wave][b] = 0u;
-#pragma unroll
-    for (int i = 0; i < kSmallItems; ++i)
-      if (base + i < n && (key[i] & mask) == prefix) atomicAdd(&wh[wave][(key[i] >> shift) & 255ull], 1u);
-    __syncthreads();
-    if (t < 256) {
-      unsigned int c = 0u;
-#pragma unroll
-      for (int w = 0; w < kSmallWaves; ++w) c += wh[w][t];
-      cnt[t] = c;
-    }
-    __syncthreads();
-    if (wave == 0) {
-      // lane l holds bins 4l .. 4l+3; above = matching keys in higher bins
-      unsigned int c4[4];
-      unsigned int v = 0u;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        c4[j] = cnt[4 * lane + j];
-        v += c4[j];
-      }
-      unsigned int suf = v;  // sum over lanes >= lane
-#pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const unsigned int u = __shfl_down(suf, off, 64);
-        if (lane + off < 64) suf += u;
-      }
-      long long above = (long long)(suf - v);
-#pragma unroll
-      for (int j = 3; j >= 0; --j) {
-        if (above < rem && rem <= above + (long long)c4[j]) {  // exactly one bin qualifies
-          s_prefix = prefix | ((unsigned long long)(4 * lane + j) << shift);
-          s_mask = mask | (255ull << shift);
-          s_rem = rem - above;
-        }
-        above += c4[j];
-      }
-    }
-    __syncthreads();
-    prefix = s_prefix;
-    mask = s_mask;
-    rem = s_rem;
-  }
-
-  // prefix is now the k-th largest key T; rem = rows equal to T to take
-  unsigned int eq_t = 0u;
-#pragma unroll
-  for (int i = 0; i < kSmallItems; ++i) eq_t += (base + i < n) && key[i] == prefix;
-  unsigned int tot;
-  long long rank = scan1024(eq_t, wsum, tot);
-  unsigned int take = 0u, sel_t = 0u;
-#pragma unroll
-  for (int i = 0; i < kSmallItems; ++i) {
-    const bool valid = base + i < n;
-    const bool is_eq = valid && key[i] == prefix;
-    const bool tk = valid && (key[i] > prefix || (is_eq && rank < rem));
-    rank += is_eq;
-    take |= (unsigned int)tk << i;
-    sel_t += tk;
-  }
-  long long o = scan1024(sel_t, wsum, tot);
-#pragma unroll
-  for (int i = 0; i < kSmallItems; ++i)
-    if ((take >> i & 1u) && o < k) out[o++] = (int32_t)(base + i);  // o < k always; kept in bounds
   for (long long i = t; i < n_append; i += kSmallThreads) out[k + i] = (int32_t)(n + i);
+  const int base = t * ITEMS, nv = (int)n;
+  unsigned long long key[ITEMS];
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i) key[i] = (base + i < nv) ? order_key(dev[base + i]) : 0ull;
+#pragma unroll
+  for (int b = t; b < kSmallBins; b += kSmallThreads) hist[b] = 0u;
+  if (t == 0) s_cand = 0u;
+  unsigned long long hi = 0ull, neg = 0ull;  // largest key, largest ~key
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i)
+    if (base + i < nv) {
+      hi = key[i] > hi ? key[i] : hi;
+      neg = ~key[i] > neg ? ~key[i] : neg;
+    }
+  wave_max2(hi, neg);
+  if (lane == 0) {
+    smax[wave] = hi;
+    sneg[wave] = neg;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kSmallWaves; ++w) {
+    hi = smax[w] > hi ? smax[w] : hi;
+    neg = sneg[w] > neg ? sneg[w] : neg;
+  }
+  Bracket b = {~neg, span_bits(~neg, hi), k, (unsigned int)n};
+  while (!b.done()) {
+    const int shift = b.bits > 11 ? b.bits - 11 : 0;
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i)
+      if (base + i < nv && b.in(key[i])) atomicAdd(&hist[(key[i] - b.lo) >> shift], 1u);
+    __syncthreads();
+    // thread t holds bins 2 t and 2 t + 1; keys in higher bins = all - those up to here
+    const unsigned int c0 = hist[2 * t], c1 = hist[2 * t + 1];
+    unsigned int tot;
+    const unsigned int before = block_scan<kSmallWaves>(c0 + c1, wsum, tot);
+    hist[2 * t] = 0u;
+    hist[2 * t + 1] = 0u;
+    const long long above1 = (long long)(tot - before - c0 - c1), above0 = above1 + c1;
+    if (above1 < b.rem && b.rem <= above0)
+      s_next = {b.lo + ((unsigned long long)(2 * t + 1) << shift), shift, b.rem - above1, c1};
+    else if (above0 < b.rem && b.rem <= above0 + c0)
+      s_next = {b.lo + ((unsigned long long)(2 * t) << shift), shift, b.rem - above0, c0};
+    __syncthreads();  // exactly one bin qualifies
+    b = s_next;
+    __syncthreads();
+  }
+  unsigned int take = 0u, in = 0u;
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i)
+    if (base + i < nv) {
+      take |= (unsigned int)b.above(key[i]) << i;
+      in |= (unsigned int)b.in(key[i]) << i;
+    }
+  unsigned int tot;
+  if (b.all()) {
+    take |= in;
+  } else if (b.few()) {
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i)
+      if (in >> i & 1u) {
+        const unsigned int j = atomicAdd(&s_cand, 1u);
+        ck[j] = key[i];
+        cr[j] = base + i;
+      }
+    __syncthreads();
+    const int nc = (int)s_cand;
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i)
+      if ((in >> i & 1u) && rank_of(key[i], base + i, ck, cr, nc) < b.rem) take |= 1u << i;
+  } else {  // equal keys: by row
+    long long rank = block_scan<kSmallWaves>((unsigned int)__popc(in), wsum, tot);
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i)
+      if (in >> i & 1u) take |= (unsigned int)(rank++ < b.rem) << i;
+  }
+  long long o = block_scan<kSmallWaves>((unsigned int)__popc(take), wsum, tot);
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i)
+    if ((take >> i & 1u) && o < k) out[o++] = (int32_t)(base + i);  // o < k always; kept in bounds
 }
 
+template <int ITEMS>
+hipError_t launch_small(const double* dev, int64_t n, int64_t k, int64_t n_append, int32_t* out, hipStream_t s) {
+  hipLaunchKernelGGL(topk_small<ITEMS>, dim3(1), dim3(kSmallThreads), 0, s, dev, (long long)n, (long long)k,
+                     (long long)n_append, out);
+  return hipGetLastError();
+}
 
-// ---- fused path: all passes in one launch ------------------------------------
+// ---- fused path: all steps in one launch -------------------------------------
 // From 16,385 to kFusedMaxRows candidates: one workgroup per 2,048 rows (at
 // most 128, so every workgroup is resident at once on the 256 CUs), each
-// thread keeping its 8 consecutive rows' keys in registers.  The passes and
-// the ordered write are separated by grid barriers (an arrival counter in
-// the workspace); after each pass every workgroup reads the same byte
-// histogram and picks the same byte, so no workgroup has to publish it.
-// Pass p adds into histogram p % 3; after barrier p, workgroup 0 clears
-// histogram (p + 2) % 3, which every workgroup finished reading before it
-// arrived at barrier p and which nobody adds into before barrier p + 1.
-// Two launches instead of eleven, and the keys are read once (124k: 42 us
-// instead of 90).
+// thread keeping its 8 consecutive rows' keys in registers.  The steps are
+// separated by grid barriers (an arrival counter in the workspace); after
+// each histogram every workgroup reads it and picks the same bin, so no
+// workgroup has to publish it.  Histogram h adds into array h % 3; after its
+// barrier, workgroup 0 clears array (h + 2) % 3, which every workgroup
+// finished reading before it arrived there and which nobody adds into before
+// the next barrier.  Once the rest is decided the other two arrays hold the
+// candidates.  Four barriers (range, two histograms, counts and candidates)
+// where eight byte passes took nine: 32,000 candidates 34 -> 19 us, 124,000
+// 38 -> 22 us, and in a layer the deviation's launch zeroes the state (4.7 us
+// for a launch of its own).
 constexpr int kFusedMaxBlocks = 128;
 constexpr long long kFusedMaxRows = (long long)kFusedMaxBlocks * kTopkRowsPerBlock;
+constexpr int kFusedWaves = kThreads / 64;
 // A bound on every barrier wait (seconds), so that no wait is endless: it is
 // reached only if some workgroup of the grid cannot run at all, which at
 // most 128 workgroups of 256 threads on 256 CUs does not happen (the other
 // kernels that may share the GPU, on other streams, all finish on their
 // own); the selection would then be wrong.
 constexpr int kSpinLimit = 1 << 22;
+static_assert(sizeof(TopkFused::hist[0]) == kThreads * 4 && kMaxCand * 8 <= kThreads * 4, "candidates fit a histogram");
 
 __global__ __launch_bounds__(kThreads) void topk_fused_init(TopkFused* st) {
-  const int t = threadIdx.x;
-  st->hist[0][t] = 0u;
-  st->hist[1][t] = 0u;
-  if (t == 0) st->arrive = 0u;
+  unsigned int* w = reinterpret_cast<unsigned int*>(st);
+  for (int i = threadIdx.x; i < (int)(sizeof(TopkFused) / 4); i += kThreads) w[i] = 0u;
+}
+
+__device__ __forceinline__ unsigned int load_dev(const unsigned int* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void store_dev(unsigned int* p, unsigned int v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Every workgroup of the grid arrives once per barrier id; returns when all
 // have arrived at barrier id (or the spin bound is reached).  Everything the
-// workgroups exchange (histogram adds and clears, block counts, the arrival
-// counter) is a device-scope atomic, performed where all XCDs see it, so
-// the barrier needs no cache writeback: each wave waits until its own
-// atomics are done before the workgroup arrives, and a workgroup reads the
-// exchanged values only after it has seen every arrival.
+// workgroups exchange (histogram adds and clears, the range, block counts,
+// candidates, the arrival counter) is a device-scope atomic, performed where
+// all XCDs see it, so the barrier needs no cache writeback: each wave waits
+// until its own atomics are done before the workgroup arrives, and a
+// workgroup reads the exchanged values only after it has seen every arrival.
 __device__ __forceinline__ void grid_barrier(TopkFused* st, unsigned int id) {
   __builtin_amdgcn_s_waitcnt(0);  // this wave's adds and stores are done
   __syncthreads();
@@ -355,8 +426,8 @@ __device__ __forceinline__ void grid_barrier(TopkFused* st, unsigned int id) {
     __hip_atomic_fetch_add(&st->arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const unsigned int target = (id + 1u) * gridDim.x;
     for (int it = 0; it < kSpinLimit; ++it) {
-      if (__hip_atomic_load(&st->arrive, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= target) break;
-      __builtin_amdgcn_s_sleep(2);
+      if (load_dev(&st->arrive) >= target) break;
+      __builtin_amdgcn_s_sleep(1);
     }
   }
   __syncthreads();
@@ -366,106 +437,136 @@ __global__ __launch_bounds__(kThreads) void topk_fused(const double* __restrict_
                                                        long long n_append, TopkFused* st,
                                                        unsigned int* __restrict__ bc, int32_t* __restrict__ out) {
   __shared__ unsigned int h[kThreads];
-  __shared__ unsigned int sh[kThreads];
-  __shared__ unsigned long long s_prefix, s_mask, red[2];
-  __shared__ long long s_rem;
-  const int t = threadIdx.x;
+  __shared__ unsigned int wsum[kFusedWaves];
+  __shared__ unsigned long long smax[kFusedWaves], sneg[kFusedWaves];
+  __shared__ unsigned long long ck[kMaxCand];
+  __shared__ int cr[kMaxCand];
+  __shared__ Bracket s_next;
+  __shared__ unsigned int red[2];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const long long base = (long long)blockIdx.x * kTopkRowsPerBlock + (long long)t * kItems;
+  for (long long i = (long long)blockIdx.x * kThreads + t; i < n_append; i += (long long)gridDim.x * kThreads)
+    out[k + i] = (int32_t)(n + i);
   unsigned long long key[kItems];
   unsigned int valid = 0u;
+  unsigned long long hi = 0ull, neg = 0ull;  // largest key, largest ~key
 #pragma unroll
   for (int i = 0; i < kItems; ++i) {
     const bool v = base + i < n;
     key[i] = v ? order_key(dev[base + i]) : 0ull;
     valid |= (unsigned int)v << i;
+    hi = key[i] > hi ? key[i] : hi;
+    const unsigned long long c = v ? ~key[i] : 0ull;
+    neg = c > neg ? c : neg;
   }
-  unsigned long long prefix = 0ull, mask = 0ull;
-  long long rem = k;
-  for (int pass = 0; pass < 8; ++pass) {
-    const int shift = 56 - 8 * pass;
-    unsigned int* gh = st->hist[pass % 3];
-    h[t] = 0u;
-    __syncthreads();
+  wave_max2(hi, neg);
+  if (lane == 0) {
+    smax[wave] = hi;
+    sneg[wave] = neg;
+  }
+  h[t] = 0u;
+  __syncthreads();
+  if (t == 0) {
+#pragma unroll
+    for (int w = 1; w < kFusedWaves; ++w) {
+      hi = smax[w] > hi ? smax[w] : hi;
+      neg = sneg[w] > neg ? sneg[w] : neg;
+    }
+    __hip_atomic_fetch_max(&st->max_key, hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_fetch_max(&st->max_not, neg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  unsigned int bar = 0u;
+  grid_barrier(st, bar++);
+  hi = __hip_atomic_load(&st->max_key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  neg = __hip_atomic_load(&st->max_not, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  Bracket b = {~neg, span_bits(~neg, hi), k, (unsigned int)n};
+  int level = 0;
+  while (!b.done()) {
+    const int shift = b.bits > 8 ? b.bits - 8 : 0;
+    unsigned int* gh = st->hist[level % 3];
 #pragma unroll
     for (int i = 0; i < kItems; ++i)
-      if ((valid >> i & 1u) && (key[i] & mask) == prefix) atomicAdd(&h[(key[i] >> shift) & 255ull], 1u);
+      if ((valid >> i & 1u) && b.in(key[i])) atomicAdd(&h[(key[i] - b.lo) >> shift], 1u);
     __syncthreads();
     if (h[t]) atomicAdd(&gh[t], h[t]);
-    grid_barrier(st, (unsigned int)pass);
-    const unsigned int cnt = __hip_atomic_load(&gh[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (blockIdx.x == 0 && pass + 2 < 8)
-      __hip_atomic_store(&st->hist[(pass + 2) % 3][t], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // suf[b] = matching keys whose byte is >= b
-    sh[t] = cnt;
+    h[t] = 0u;
+    grid_barrier(st, bar++);
+    const unsigned int c = load_dev(&gh[t]);
+    unsigned int tot;
+    const unsigned int before = block_scan<kFusedWaves>(c, wsum, tot);
+    const long long above = (long long)(tot - before - c);
+    if (above < b.rem && b.rem <= above + c)  // exactly one bin qualifies
+      s_next = {b.lo + ((unsigned long long)t << shift), shift, b.rem - above, c};
     __syncthreads();
-#pragma unroll
-    for (int off = 1; off < kThreads; off <<= 1) {
-      const unsigned int add = (t + off < kThreads) ? sh[t + off] : 0u;
-      __syncthreads();
-      sh[t] += add;
-      __syncthreads();
-    }
-    const long long above = (long long)(sh[t] - cnt);
-    if (above < rem && rem <= (long long)sh[t]) {  // exactly one byte value qualifies
-      s_prefix = prefix | ((unsigned long long)t << shift);
-      s_mask = mask | (255ull << shift);
-      s_rem = rem - above;
-    }
-    __syncthreads();
-    prefix = s_prefix;
-    mask = s_mask;
-    rem = s_rem;
-    __syncthreads();  // sh and the shared prefix are rewritten by the next pass
+    b = s_next;
+    __syncthreads();  // s_next is rewritten by the next level
+    if (blockIdx.x == 0 && !b.done()) store_dev(&st->hist[(level + 2) % 3][t], 0u);
+    ++level;
   }
-  // prefix is the k-th largest key T; rem = rows equal to T still to take.
-  // Per workgroup: rows above T and rows equal to T, then the ordered write.
-  const unsigned long long T = prefix;
-  unsigned int gt_t = 0u, eq_t = 0u;
+  // Per workgroup: rows above the bracket and (equal keys) in it, and the
+  // candidates, then the ordered write.
+  unsigned int take = 0u, in = 0u;
 #pragma unroll
-  for (int i = 0; i < kItems; ++i) {
-    const bool v = valid >> i & 1u;
-    gt_t += v && key[i] > T;
-    eq_t += v && key[i] == T;
+  for (int i = 0; i < kItems; ++i)
+    if (valid >> i & 1u) {
+      take |= (unsigned int)b.above(key[i]) << i;
+      in |= (unsigned int)b.in(key[i]) << i;
+    }
+  const bool few = !b.all() && b.few(), ties = !b.all() && !b.few();
+  if (b.all()) take |= in;
+  unsigned int tot_take, tot_in = 0u, in_before = 0u;
+  block_scan<kFusedWaves>((unsigned int)__popc(take), wsum, tot_take);
+  if (ties) in_before = block_scan<kFusedWaves>((unsigned int)__popc(in), wsum, tot_in);
+  // array level % 3 was last read (or never used), the one after it is clean
+  unsigned long long* gk = reinterpret_cast<unsigned long long*>(st->hist[level % 3]);
+  unsigned int* gr = st->hist[(level + 1) % 3];
+  if (few) {
+#pragma unroll
+    for (int i = 0; i < kItems; ++i)
+      if (in >> i & 1u) {
+        const unsigned int j = atomicAdd(&st->cand, 1u);
+        __hip_atomic_store(&gk[j], key[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        store_dev(&gr[j], (unsigned int)(base + i));
+      }
   }
-  unsigned int tot_gt, tot_eq;
-  block_excl_scan(gt_t, sh, tot_gt);
-  const unsigned int eq_excl = block_excl_scan(eq_t, sh, tot_eq);
   if (t == 0) {
-    __hip_atomic_store(&bc[2 * blockIdx.x], tot_gt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(&bc[2 * blockIdx.x + 1], tot_eq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    red[0] = 0ull;
-    red[1] = 0ull;
+    store_dev(&bc[2 * blockIdx.x], tot_take);
+    store_dev(&bc[2 * blockIdx.x + 1], tot_in);
+    red[0] = 0u;
+    red[1] = 0u;
   }
-  grid_barrier(st, 8u);
-  unsigned long long gtb = 0ull, eqb = 0ull;
-  for (int b = t; b < (int)blockIdx.x; b += kThreads) {
-    gtb += __hip_atomic_load(&bc[2 * b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    eqb += __hip_atomic_load(&bc[2 * b + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  grid_barrier(st, bar++);
+  if (t < (int)blockIdx.x) {  // at most 128 workgroups
+    atomicAdd(&red[0], load_dev(&bc[2 * t]));
+    if (ties) atomicAdd(&red[1], load_dev(&bc[2 * t + 1]));
   }
-  if (gtb) atomicAdd(&red[0], gtb);
-  if (eqb) atomicAdd(&red[1], eqb);
+  const int nc = few ? (int)b.count : 0;
+  if (t < nc) {
+    ck[t] = __hip_atomic_load(&gk[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    cr[t] = (int)load_dev(&gr[t]);
+  }
   __syncthreads();
-  const long long gt_before = (long long)red[0];
-  const long long eq_before = (long long)red[1];
-  const long long sel_before = gt_before + (eq_before < rem ? eq_before : rem);
-  unsigned int take = 0u, sel_t = 0u;
-  long long rank = eq_before + eq_excl;
+  long long sel_before = red[0];
+  if (few) {
 #pragma unroll
-  for (int i = 0; i < kItems; ++i) {
-    const bool v = valid >> i & 1u;
-    const bool is_eq = v && key[i] == T;
-    const bool tk = v && (key[i] > T || (is_eq && rank < rem));
-    rank += is_eq;
-    take |= (unsigned int)tk << i;
-    sel_t += tk;
+    for (int i = 0; i < kItems; ++i)
+      if ((in >> i & 1u) && rank_of(key[i], (int)(base + i), ck, cr, nc) < b.rem) take |= 1u << i;
+    // candidates taken in earlier workgroups
+    const bool earlier = t < nc && cr[t] < (int)(blockIdx.x * kTopkRowsPerBlock) && rank_of(ck[t], cr[t], ck, cr, nc) < b.rem;
+    sel_before += __syncthreads_count(earlier);
+  } else if (ties) {
+    const long long eq_before = red[1];
+    sel_before += eq_before < b.rem ? eq_before : b.rem;
+    long long rank = eq_before + in_before;
+#pragma unroll
+    for (int i = 0; i < kItems; ++i)
+      if (in >> i & 1u) take |= (unsigned int)(rank++ < b.rem) << i;
   }
   unsigned int tot;
-  long long o = sel_before + block_excl_scan(sel_t, sh, tot);
+  long long o = sel_before + block_scan<kFusedWaves>((unsigned int)__popc(take), wsum, tot);
 #pragma unroll
   for (int i = 0; i < kItems; ++i)
     if ((take >> i & 1u) && o < k) out[o++] = (int32_t)(base + i);  // o < k always; kept in bounds
-  for (long long i = (long long)blockIdx.x * kThreads + t; i < n_append; i += (long long)gridDim.x * kThreads)
-    out[k + i] = (int32_t)(n + i);
 }
 
 // out[i] = start + i for i < count
@@ -486,21 +587,25 @@ hipError_t launch_iota(int32_t* out, long long count, long long start, hipStream
 
 }  // namespace
 
+size_t topk_clear_bytes(int64_t n) { return n > kSmallMax && n <= kFusedMaxRows ? sizeof(TopkFused) : 0; }
+
 hipError_t launch_select_topk(const double* dev, int64_t n, int64_t k, int64_t n_append,
-                              int32_t* idx_out, void* ws, hipStream_t s) {
+                              int32_t* idx_out, void* ws, bool cleared, hipStream_t s) {
   if (k == 0) return launch_iota(idx_out, n_append, n, s);
   if (k == n) return launch_iota(idx_out, n + n_append, 0, s);
   if (n <= kSmallMax) {
-    hipLaunchKernelGGL(topk_small, dim3(1), dim3(kSmallThreads), 0, s, dev, (long long)n, (long long)k,
-                       (long long)n_append, idx_out);
-    return hipGetLastError();
+    if (n <= kSmallThreads) return launch_small<1>(dev, n, k, n_append, idx_out, s);
+    if (n <= 2 * kSmallThreads) return launch_small<2>(dev, n, k, n_append, idx_out, s);
+    if (n <= 4 * kSmallThreads) return launch_small<4>(dev, n, k, n_append, idx_out, s);
+    if (n <= 8 * kSmallThreads) return launch_small<8>(dev, n, k, n_append, idx_out, s);
+    return launch_small<16>(dev, n, k, n_append, idx_out, s);
   }
   const size_t state = sizeof(TopkState) > sizeof(TopkFused) ? sizeof(TopkState) : sizeof(TopkFused);
   unsigned int* bc = reinterpret_cast<unsigned int*>(static_cast<char*>(ws) + align256(state));
   const long long nblk = topk_blocks(n);
   if (n <= kFusedMaxRows) {
     TopkFused* fs = static_cast<TopkFused*>(ws);
-    hipLaunchKernelGGL(topk_fused_init, dim3(1), dim3(kThreads), 0, s, fs);
+    if (!cleared) hipLaunchKernelGGL(topk_fused_init, dim3(1), dim3(kThreads), 0, s, fs);
     hipLaunchKernelGGL(topk_fused, dim3((unsigned)nblk), dim3(kThreads), 0, s, dev, (long long)n, (long long)k,
                        (long long)n_append, fs, bc, idx_out);
     return hipGetLastError();

@@ -362,6 +362,29 @@ def test_select_topk_ties_go_to_lower_rows(K, levels, n):
         assert np.array_equal(_topk_gpu(K, d, k), oracle.select_topk(d, k))
 
 
+# Keys per thread and workgroup (1 to 16 per thread, one or many workgroups)
+# against what ends the search for the threshold: a bracket with 127 to 130
+# keys (ranked one by one up to 128), all keys of it taken, equal keys, and
+# keys from the whole float64 range (many histograms).
+@pytest.mark.parametrize("n", [129, 1024, 1025, 4096, 4097, 16384, 16385, 34816, 262144])
+def test_select_topk_brackets(K, n):
+    rng = np.random.default_rng(n)
+    near = 1.0 + rng.permutation(n) * 2.0 ** -52           # neighbours in float64
+    for m in (127, 128, 129, 130):
+        d = np.full(n, 0.5)
+        d[rng.choice(n, min(m, n), replace=False)] = near[:min(m, n)]
+        d[rng.choice(n, min(n, 3), replace=False)] = 1e300
+        for k in (1, min(60, n - 1), min(m, n - 1), min(m + 5, n - 1)):
+            assert np.array_equal(_topk_gpu(K, d, k), oracle.select_topk(d, k)), (m, k)
+    bits = rng.integers(0, 2 ** 64, n, dtype=np.uint64)
+    wide = bits.view(np.float64).copy()
+    wide[~np.isfinite(wide)] = 0.0
+    some = np.where(rng.random(n) < 0.6, 0.0, rng.random(n))
+    for d in (wide, some, np.abs(wide)):
+        for k in (1, n // 7 + 1, n // 2, n - 1):
+            assert np.array_equal(_topk_gpu(K, d, k), oracle.select_topk(d, k)), k
+
+
 @pytest.mark.parametrize("m", [3000, 12000, 20000])
 def test_select_topk_signed_and_extreme_values(K, m):
     rng = np.random.default_rng(5)
