@@ -270,15 +270,24 @@ hipError_t shift_and_select(const kvc_layout* L, const LayoutInfo& li, const kvc
                             int32_t* sel, void* ws, hipStream_t s) {
   const int hkv = L->n_kv_heads;
   hipError_t e;
+  const bool select = check && k > 0 && k < li.n_reused;
+  // the deviation vector, then the selection's state
+  double* dev = static_cast<double*>(ws);
+  void* tws = select ? static_cast<char*>(ws) + kvc::align256(sizeof(double) * (size_t)li.n_reused) : nullptr;
+  if (select && k_src && kvc::shift_deviation_fits(li.n_reused, hkv)) {
+    e = kvc::launch_shift_deviation(plan->device, plan->layout_id, L->n_chunks, li.n_tiles, hkv,
+                                    static_cast<const uint16_t*>(k_src), static_cast<uint16_t*>(k_cache),
+                                    static_cast<const uint16_t*>(k_fresh), dev, s);
+    if (e != hipSuccess) return e;
+    return kvc::launch_select_topk(dev, li.n_reused, k, L->n_query, sel, tws, false, s);
+  }
   if (li.n_reused > 0 && k_src) {
     e = kvc::launch_rope_shift(plan->device, plan->layout_id, L->n_chunks, li.n_tiles, hkv, static_cast<const uint16_t*>(k_src),
                                static_cast<uint16_t*>(k_cache), nullptr, s);
     if (e != hipSuccess) return e;
   }
   if (!check || k + L->n_query == 0) return hipSuccess;
-  if (k > 0 && k < li.n_reused) {
-    double* dev = static_cast<double*>(ws);
-    void* tws = static_cast<char*>(ws) + kvc::align256(sizeof(double) * (size_t)li.n_reused);
+  if (select) {
     e = kvc::launch_kv_deviation(li.n_reused, hkv, static_cast<const uint16_t*>(k_cache),
                                  static_cast<const uint16_t*>(k_fresh), dev, tws, kvc::topk_clear_bytes(li.n_reused), s);
     if (e != hipSuccess) return e;

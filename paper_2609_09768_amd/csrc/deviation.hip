@@ -45,6 +45,7 @@
 // float64 (nearest, ties to even, sticky bit from everything below).
 #include "kvc_internal.h"
 #include "bf16_util.h"
+#include "rope_rotate.h"
 
 // Every floating-point operation here is written to round exactly where it
 // is written: a product fused into a following sum (the compiler's default
@@ -360,6 +361,98 @@ __global__ __launch_bounds__(kThreads) void kv_deviation_rows_kernel(const uint1
   }
 }
 
+// Adjustment and deviation in one launch, for small requests: one workgroup
+// per shift tile (at most 16 rows there), LPR lanes per row, each lane UPL
+// units (8 pairs of one head: 16 bytes of each half), rotated, stored and
+// compared while in registers.  Such a request is bound by launches, not
+// bytes: at 1,024 rows of 2 heads this takes 4.9 us (3.6 + 4.8 apart), at
+// 4,000 of 8 10.1 us (6.0 + 6.8).  The float64 work of both in tiles this
+// small costs more than the second pass over the keys from about 40,000 rows
+// x heads on: selection of 4,000 / 6,000 rows of 8 heads 19.0 / 28.5 us
+// against 22 / 26.9 apart, of 8,000 / 12,000 of 4 heads 23.2 / 33.8 against
+// 25.3 / 34.5, of 16,000 of 2 heads 35.0 against 37.6.
+template <int WAVES, int LPR, int UPL>
+__global__ __launch_bounds__(64 * WAVES) void shift_deviation_kernel(
+    const PlanHeader* __restrict__ hdr, const ShiftTile* __restrict__ tiles, uint64_t layout_hash,
+    const uint16_t* src /* may equal dst */, uint16_t* dst, const uint16_t* __restrict__ kf, double* __restrict__ dev,
+    int in_place, const double2* __restrict__ rot_table) {
+  constexpr int kRpw = 64 / LPR;
+  constexpr int kRowElems = LPR * UPL * 16;
+  constexpr int kPieces = 2 * LPR * UPL;
+  __shared__ unsigned long long sacc[WAVES][kRpw][kDigits];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int sub = lane / LPR, p = lane % LPR, jg = p & 7;
+  const ShiftTile t = tiles[blockIdx.x];
+  // a plan buffer overwritten since its descriptor was made is not used
+  if ((hdr->layout_hash != layout_hash) | (t.row_end < t.row_begin) | (t.chunk < 0) |
+      (t.flags > (kTileDeltaZero | kTileZeroKv)))
+    return;
+  const bool keep = in_place && (t.flags & kTileDeltaZero);
+  double c[8], s[8];
+  const double2* rot = rot_table + (size_t)t.chunk * kHalf + jg * 8;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const double2 cs = rot[e];
+    c[e] = cs.x;
+    s[e] = cs.y;
+  }
+  for (int64_t r0 = t.row_begin + wave * kRpw; r0 < t.row_end; r0 += WAVES * kRpw) {
+    const int64_t r = r0 + sub;
+    const bool valid = r < t.row_end;
+    uint4 a[UPL], b[UPL], fa[UPL], fb[UPL];
+#pragma unroll
+    for (int i = 0; i < UPL; ++i) {
+      a[i] = b[i] = fa[i] = fb[i] = make_uint4(0, 0, 0, 0);
+      if (valid) {
+        const int64_t off = r * kRowElems + ((p + LPR * i) >> 3) * kHeadDim + jg * 8;
+        a[i] = load_nt(src + off);
+        b[i] = load_nt(src + off + kHalf);
+        fa[i] = load_nt(kf + off);
+        fb[i] = load_nt(kf + off + kHalf);
+      }
+    }
+    double hi = 0.0, lo = 0.0;
+    uint32_t mx = 0, mn = 0;
+#pragma unroll
+    for (int i = 0; i < UPL; ++i) {
+      if (!keep) {
+        uint4 oa, ob;
+        rotate8(a[i], b[i], c, s, oa, ob);
+        a[i] = oa;
+        b[i] = ob;
+        if (valid) {
+          const int64_t off = r * kRowElems + ((p + LPR * i) >> 3) * kHeadDim + jg * 8;
+          *reinterpret_cast<uint4*>(dst + off) = oa;
+          *reinterpret_cast<uint4*>(dst + off + kHalf) = ob;
+        }
+      }
+      accumulate8(fa[i], a[i], hi, lo, mx, mn);
+      accumulate8(fb[i], b[i], hi, lo, mx, mn);
+    }
+    uint32_t rng = fold_range(mx, mn);
+#pragma unroll
+    for (int m = LPR / 2; m >= 1; m >>= 1) merge(hi, lo, rng, m);
+    double y;
+    if (valid && !fast_result_exact(hi, lo, rng, kPieces * 8, y)) {  // uniform within the row's lanes
+      // the adjusted row is read again: this wave wrote it, wait until it can be
+      __threadfence();
+      y = exact_row(sacc[wave][sub], reinterpret_cast<const uint4*>(kf), reinterpret_cast<const uint4*>(dst), r, kPieces,
+                    p, LPR);
+    }
+    if (p == 0 && valid) dev[r] = y;
+  }
+}
+
+template <int WAVES, int LPR, int UPL>
+hipError_t launch_shift_dev(const char* plan, uint64_t layout_hash, int n_chunks, int n_tiles, const uint16_t* src,
+                            uint16_t* dst, const uint16_t* kf, double* dev, hipStream_t s) {
+  hipLaunchKernelGGL((shift_deviation_kernel<WAVES, LPR, UPL>), dim3((unsigned)n_tiles), dim3(64 * WAVES), 0, s,
+                     reinterpret_cast<const PlanHeader*>(plan),
+                     reinterpret_cast<const ShiftTile*>(plan + plan_tile_offset(n_chunks)), layout_hash, src, dst, kf,
+                     dev, (int)(src == dst), reinterpret_cast<const double2*>(plan + plan_rot_offset()));
+  return hipGetLastError();
+}
+
 template <int LPR, int PPL, int STEPS>
 hipError_t launch_rows(int64_t n_rows, const uint16_t* kc, const uint16_t* kf, double* dev, ClearArgs clear,
                        hipStream_t s) {
@@ -384,6 +477,23 @@ hipError_t launch_cpl(int64_t n_rows, int pieces, const uint16_t* kc, const uint
 }
 
 }  // namespace
+
+bool shift_deviation_fits(int64_t n_reused, int n_kv_heads) {
+  return n_reused > 0 && n_reused < 16384 && n_reused * n_kv_heads <= 40000 &&
+         (n_kv_heads == 1 || n_kv_heads == 2 || n_kv_heads == 4 || n_kv_heads == 8);
+}
+
+hipError_t launch_shift_deviation(const void* plan, uint64_t layout_hash, int n_chunks, int n_tiles, int n_kv_heads,
+                                  const uint16_t* k_src, uint16_t* k_dst, const uint16_t* k_fresh, double* dev,
+                                  hipStream_t s) {
+  const char* p = static_cast<const char*>(plan);
+  switch (n_kv_heads) {  // 16 rows in one pass of the workgroup
+    case 1: return launch_shift_dev<2, 8, 1>(p, layout_hash, n_chunks, n_tiles, k_src, k_dst, k_fresh, dev, s);
+    case 2: return launch_shift_dev<4, 16, 1>(p, layout_hash, n_chunks, n_tiles, k_src, k_dst, k_fresh, dev, s);
+    case 4: return launch_shift_dev<4, 16, 2>(p, layout_hash, n_chunks, n_tiles, k_src, k_dst, k_fresh, dev, s);
+    default: return launch_shift_dev<8, 32, 2>(p, layout_hash, n_chunks, n_tiles, k_src, k_dst, k_fresh, dev, s);
+  }
+}
 
 hipError_t launch_kv_deviation(int64_t n_rows, int n_kv_heads, const uint16_t* k_cached,
                                const uint16_t* k_fresh, double* dev, void* clear_p, size_t clear_bytes,

@@ -92,6 +92,11 @@ hipError_t launch_rope_shift(const void* plan, uint64_t layout_hash, int n_chunk
 hipError_t launch_kv_deviation(int64_t n_rows, int n_kv_heads, const uint16_t* k_cached,
                                const uint16_t* k_fresh, double* dev, void* clear, size_t clear_bytes,
                                hipStream_t s);
+// Adjustment and deviation in one launch, for the small requests it fits.
+bool shift_deviation_fits(int64_t n_reused, int n_kv_heads);
+hipError_t launch_shift_deviation(const void* plan, uint64_t layout_hash, int n_chunks, int n_tiles, int n_kv_heads,
+                                  const uint16_t* k_src, uint16_t* k_dst, const uint16_t* k_fresh, double* dev,
+                                  hipStream_t s);
 // Bytes at the start of the selection's workspace to be zero when it starts.
 size_t topk_clear_bytes(int64_t n);
 // cleared: they are; otherwise a launch of its own does it.

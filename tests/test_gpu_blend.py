@@ -8,11 +8,12 @@ import os
 
 import numpy as np
 import pytest
+import torch
 
 import oracle
 import workloads as W
 from _blend import gpu_layer, oracle_layer, layout
-from _gpu import within_tol, LSE_ATOL
+from _gpu import up, bytes_buf, within_tol, LSE_ATOL
 from _inputs import build
 
 pytestmark = pytest.mark.gpu
@@ -262,3 +263,52 @@ def test_multi_layer_prefill_reuses_the_selection(K, check_at):
         assert ok, (layer, err)
     for layer in range(check_at + 1, 4):
         assert np.array_equal(sels[layer], sels[check_at])   # selection untouched
+
+
+@pytest.mark.parametrize("in_place", [False, True])
+@pytest.mark.parametrize("n_kv_heads,lens", [(1, (7, 0, 33, 200, 16, 1)), (2, (17, 300, 5)), (4, (64, 31, 2)),
+                                             (8, (250, 3, 16, 90)), (3, (40, 60))])
+def test_select_tokens_small_requests(K, n_kv_heads, lens, in_place):
+    """A small request adjusts and compares in one launch (1, 2, 4 or 8 kv
+    heads): the same keys, bit for bit, and the same selection as the steps on
+    their own, and rows whose deviations only an exactly rounded sum tells
+    apart."""
+    rng = np.random.default_rng(n_kv_heads + 10 * len(lens))
+    n_r, n_q = sum(lens), 3
+    row0 = np.concatenate([[0], np.cumsum(lens)[:-1]])
+    # the last chunk of at least 30 rows keeps its positions
+    still = [i for i, n in enumerate(lens) if n >= 30][-1]
+    old = [int(r) if i == still else int(rng.integers(-50, 50)) for i, r in enumerate(row0)]
+    L = K.Layout(lens, n_q, 2 * n_kv_heads, n_kv_heads, chunk_old_pos0=old)
+    pb = K.kvc_plan_bytes(L)
+    plan = K.kvc_plan_upload(L, bytes_buf(pb), pb)
+    k_src = rng.standard_normal((n_r, n_kv_heads, 128))
+    k_fresh = k_src + 0.1 * rng.standard_normal(k_src.shape)
+    # squares 2^52, 2^52, 1 and, in every other row, 2^-100 at random places:
+    # 2^53 + 1 + 2^-100 rounds up to 2^53 + 2, 2^53 + 1 to 2^53
+    big = np.arange(row0[still], row0[still] + lens[still])
+    k_src[big] = 0.0
+    k_fresh[big] = 0.0
+    flat = k_fresh.reshape(n_r, -1)
+    for j, r in enumerate(big):
+        at = rng.permutation(flat.shape[1])[:4]
+        flat[r, at] = [2.0 ** 26, -2.0 ** 26, 1.0, 2.0 ** -50 if j % 2 else 0.0]
+    src, fresh = up(oracle.f64_to_bf16(k_src)), up(oracle.f64_to_bf16(k_fresh))
+    for k in (len(big) // 2, len(big) + 5):
+        ratio = (k + 0.5) / n_r
+        assert K.kvc_recompute_count(ratio, n_r) == k
+        cache = src.clone() if in_place else torch.zeros_like(src)
+        sel = torch.full((k + n_q,), -1, dtype=torch.int32, device="cuda:0")
+        wb = K.kvc_blend_workspace(L)
+        K.kvc_select_tokens(L, plan, ratio, cache if in_place else src, cache, fresh, sel, k + n_q, bytes_buf(wb), wb)
+        want_c = src.clone() if in_place else torch.zeros_like(src)
+        K.kvc_rope_shift(L, plan, want_c if in_place else src, want_c)
+        dev = torch.zeros(n_r, dtype=torch.float64, device="cuda:0")
+        K.kvc_kv_deviation(n_r, n_kv_heads, 128, want_c, fresh, dev)
+        torch.cuda.synchronize()
+        assert torch.equal(cache, want_c)
+        got = sel.cpu().numpy()
+        assert np.array_equal(got[:k], oracle.select_topk(dev.cpu().numpy(), k))
+        assert np.array_equal(got[k:], np.arange(n_r, n_r + n_q))
+        if k == len(big) // 2:
+            assert np.array_equal(got[:k], big[1::2])
