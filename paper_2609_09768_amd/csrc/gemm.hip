@@ -147,6 +147,21 @@ __device__ __forceinline__ uint32_t lds_address(uint16_t* p) {
   return a;
 }
 
+// b0 .. b7 by index, as values (a choice between variables of a closure would
+// go through memory).
+__device__ __forceinline__ uint32_t pick8(int w, uint32_t b0, uint32_t b1, uint32_t b2, uint32_t b3, uint32_t b4,
+                                          uint32_t b5, uint32_t b6, uint32_t b7) {
+  uint32_t r = b0;
+  r = w == 1 ? b1 : r;
+  r = w == 2 ? b2 : r;
+  r = w == 3 ? b3 : r;
+  r = w == 4 ? b4 : r;
+  r = w == 5 ? b5 : r;
+  r = w == 6 ? b6 : r;
+  r = w == 7 ? b7 : r;
+  return r;
+}
+
 // Output row m is a gather of an invalid entry: its product is zero.
 __device__ __forceinline__ bool zero_row(const GemmParams& P, long long m) {
   if (!P.a_rows) return false;
@@ -360,9 +375,9 @@ __device__ __forceinline__ void tile_256(const GemmParams& P, const Lds& S, int 
 // 0.53 us (128) or 0.24 us (64): a 128 tile runs at 66 % and a 64 tile at
 // 36 % of the rate of a 256 tile, bound by the loads (64 and 128 bytes per
 // CU and MFMA cycle).  Against 256 x 256 tiles only: 217 x 3,584 x 18,944
-// 428 -> 74 us, 696 x 4,096 x 4,096 94 -> 33 us, 696 x 4,096 x 14,336 316 ->
-// 109 us, and with both sizes in one launch 5,056 x 4,096 x 14,336 692 ->
-// 455 us.  (128 x 256 tiles, 128 x 64 tiles and four waves with two
+// 428 -> 72 us, 696 x 4,096 x 4,096 94 -> 30 us, 696 x 4,096 x 14,336 316 ->
+// 107 us, and with both sizes in one launch 5,056 x 4,096 x 14,336 692 ->
+// 450 us.  (128 x 256 tiles, 128 x 64 tiles and four waves with two
 // workgroups per CU were slower on most shapes.)
 template <int BT, int WM, int WN, int WK>
 __device__ __forceinline__ void tile_ring(const GemmParams& P, const Lds& L, long long m0, int tn) {
@@ -394,11 +409,20 @@ __device__ __forceinline__ void tile_ring(const GemmParams& P, const Lds& L, lon
     a_src[j] = a_source(P, m0 + row) + 8 * piece;
     w_src[j] = w_source(P, n0 + row) + 8 * piece;
   }
-  auto load_unit = [&](int t, int slot, int j) __attribute__((always_inline)) {
+  // load j of slice t: rows 8 (j % 2) .. of this wave's 16, of A (j < 2) or W
+  auto load_unit = [&](int t, int slot, auto jc) __attribute__((always_inline)) {
+    constexpr int j = decltype(jc)::value;
     // a piece of the last slice past K is loaded from inside it and not used
     const int kb = SUB == 1 ? t : min(t * SUB + 16 * wave / BT, nk - 1);
-    const uint16_t* src = (j < 2 ? a_src[j] : w_src[j - 2]) + (long long)kb * kBK;
-    load_lds16(src, (j < 2 ? SA[slot] : SW[slot]) + (16 * wave + 8 * (j & 1)) * kBK);
+    load_lds16((j < 2 ? a_src[j & 1] : w_src[j & 1]) + (long long)kb * kBK,
+               (j < 2 ? SA[slot] : SW[slot]) + (16 * wave + 8 * (j & 1)) * kBK);
+  };
+  auto load_slot = [&](int t, auto slotc) __attribute__((always_inline)) {
+    constexpr int slot = decltype(slotc)::value;
+    load_unit(t, slot, Int<0>{});
+    load_unit(t, slot, Int<1>{});
+    load_unit(t, slot, Int<2>{});
+    load_unit(t, slot, Int<3>{});
   };
   const int rl = lane & 15, q = lane >> 4, sw = (rl >> 1) & 7;
   // this wave's 32-wide K step of a slice is step kg
@@ -451,7 +475,10 @@ __device__ __forceinline__ void tile_ring(const GemmParams& P, const Lds& L, lon
       }
       if (MAIN) {
         constexpr int every = NM / UPW < 2 ? 1 : 2;  // a load after every (second) MFMA
-        if (i % every == every - 1 && i / every < UPW) load_unit(t + NS, B, i / every);
+        if (i == every - 1) load_unit(t + NS, B, Int<0>{});
+        if (i == 2 * every - 1) load_unit(t + NS, B, Int<1>{});
+        if (i == 3 * every - 1) load_unit(t + NS, B, Int<2>{});
+        if (i == 4 * every - 1) load_unit(t + NS, B, Int<3>{});
       }
     });
   };
@@ -460,10 +487,10 @@ __device__ __forceinline__ void tile_ring(const GemmParams& P, const Lds& L, lon
   const int s0 = (NS - ns % NS) % NS;
   auto start = [&](auto s0c) __attribute__((always_inline)) {
     constexpr int Z = decltype(s0c)::value;
-#pragma unroll
-    for (int i = Z; i < NS; ++i)
-#pragma unroll
-      for (int j = 0; j < UPW; ++j) load_unit(i - Z, i, j);
+    if constexpr (Z <= 0) load_slot(0 - Z, Int<0>{});
+    if constexpr (Z <= 1) load_slot(1 - Z, Int<1>{});
+    if constexpr (Z <= 2) load_slot(2 - Z, Int<2>{});
+    load_slot(3 - Z, Int<3>{});
     // (the first reads stand in both branches: the wait-count pass merges
     // them into a wait for every load otherwise)
     auto first = [&]() __attribute__((always_inline)) {
@@ -472,10 +499,9 @@ __device__ __forceinline__ void tile_ring(const GemmParams& P, const Lds& L, lon
       for (int r = 0; r < NF; ++r) read_frag(Z, Z & 1, r);
     };
     if (ns >= NS) {
-#pragma unroll
-      for (int i = 0; i < Z; ++i)
-#pragma unroll
-        for (int j = 0; j < UPW; ++j) load_unit(NS - Z + i, i, j);
+      if constexpr (Z > 0) load_slot(NS - Z, Int<0>{});
+      if constexpr (Z > 1) load_slot(NS - Z + 1, Int<1>{});
+      if constexpr (Z > 2) load_slot(NS - Z + 2, Int<2>{});
       __builtin_amdgcn_s_waitcnt(wait_imm(UPW * (NS - 1), 15));
       first();
     } else {
@@ -518,10 +544,8 @@ __device__ __forceinline__ void tile_ring(const GemmParams& P, const Lds& L, lon
   // numbers, since the compiler cannot make a table of them
   const uint32_t b0 = lds_address(L.a0), b1 = lds_address(L.a1), b2 = lds_address(L.a2), b3 = lds_address(L.a3);
   const uint32_t b4 = lds_address(L.w0), b5 = lds_address(L.w1), b6 = lds_address(L.w2), b7 = lds_address(L.w3);
-  auto share = [&](int w, int d, int i) __attribute__((always_inline)) {
-    const uint32_t lo = w & 2 ? (w & 1 ? b3 : b2) : (w & 1 ? b1 : b0);
-    const uint32_t hi = w & 2 ? (w & 1 ? b7 : b6) : (w & 1 ? b5 : b4);
-    const uint32_t base = w & 4 ? hi : lo;
+  auto base_of = [=](int w) __attribute__((always_inline)) { return pick8(w, b0, b1, b2, b3, b4, b5, b6, b7); };
+  auto share = [=](uint32_t base, int d, int i) __attribute__((always_inline)) {
     return reinterpret_cast<lds_f32x4*>(base + (uint32_t)(((d - 1) * kShare + i * 256) * 4 + lane * 16));
   };
   __builtin_amdgcn_s_waitcnt(wait_imm(0, 0));
@@ -529,13 +553,15 @@ __device__ __forceinline__ void tile_ring(const GemmParams& P, const Lds& L, lon
 #pragma unroll
   for (int o = 0; o < WK; ++o) {
     if (o == kg) continue;
+    const uint32_t to = base_of(wave - kg + o);
 #pragma unroll
     for (int i = 0; i < NTO; ++i)
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) *share(wave - kg + o, kg ^ o, i * MT + mt) = acc[o * NTO + i][mt];
+      for (int mt = 0; mt < MT; ++mt) *share(to, kg ^ o, i * MT + mt) = acc[o * NTO + i][mt];
   }
   __builtin_amdgcn_s_waitcnt(wait_imm(0, 0));
   barrier_only();
+  const uint32_t mine = base_of(wave);
 #pragma unroll
   for (int o = 0; o < WK; ++o) {
     if (o != kg) continue;
@@ -556,7 +582,7 @@ __device__ __forceinline__ void tile_ring(const GemmParams& P, const Lds& L, lon
         f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int g = 0; g < WK; ++g)
-          v += g == o ? acc[o * NTO + i][mt] : *share(wave, g ^ o, i * MT + mt);
+          v += g == o ? acc[o * NTO + i][mt] : *share(mine, g ^ o, i * MT + mt);
         store4(P, m + 16 * mt, n + 16 * i, zero[mt], v, r[mt][i]);
       }
   }
@@ -585,7 +611,7 @@ __global__ __launch_bounds__(kThreads) void gemm_kernel(const GemmParams P) {
 // ---- choice of tiles -----------------------------------------------------------
 // Measured time of a tile with all CUs busy, in ns: per 64 of K, and once per
 // tile (first loads, last sums and stores).  On 50 shapes of 90 to 14,000
-// rows the split these choose was within 3 % (geometric mean) of the best of
+// rows the split these choose was within 1.1 % (geometric mean) of the best of
 // the splits tried.
 struct TileCost {
   int width;
