@@ -15,11 +15,11 @@
 // accumulator bytes per FLOP of the 32x32 one; on this power-limited chip
 // it ran 8-13 % faster on the layer's shapes, with identical results.)
 //
-// One workgroup of 8 waves (two per SIMD) computes one square tile of c over
-// the whole K.  The tile is 256, 128 or 64 wide, and a launch mixes two of
-// the three (`plan_of` below): the row count of a selection is rarely a
-// multiple of what fills 256 CUs, and a last round of a few large tiles
-// would cost as much as a full one.  Common to all tiles:
+// One workgroup of 8 waves (two per SIMD) computes one tile of c over the
+// whole K.  The tile is 256 x 256, 256 x 192, 128 x 128 or 64 x 64, and a
+// launch mixes a large and a small one (`plan_of` below): the tiles of a
+// selection rarely fill 256 CUs a whole number of times, and a last round of
+// a few large tiles would cost as much as a full one.  Common to all tiles:
 // - Activation and weight rows go from memory straight into LDS in 128-byte
 //   pieces of K (global loads with an LDS destination: per-lane 64-bit
 //   addresses, so the row gather costs nothing; no registers, no VALU).
@@ -194,10 +194,11 @@ __device__ __forceinline__ void store4(const GemmParams& P, long long m, long lo
   *reinterpret_cast<uint2*>(P.c + m * P.n + n) = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
 }
 
-// A 256 x 256 tile in K slices of 64, two of them in LDS.  Each wave owns 64
-// rows x 32 columns of each quarter of the tile.  A slice is two phases: the
-// tile's upper rows (16 fragments read, 32 MFMAs), then the lower ones (8
-// read, 32 MFMAs).  The two waves of a SIMD run half a phase apart (waves
+// A tile of 256 rows and 64 NT columns (NT = 4 or 3) in K slices of 64, two of
+// them in LDS.  Each wave owns 64 rows of each half of the tile's rows and NT
+// blocks of 16 columns, adjacent ones where it can, for the stores.  A slice is
+// two phases (figures for NT = 4): the tile's upper rows (16 fragments read,
+// 32 MFMAs), then the lower ones (8 read, 32 MFMAs).  The two waves of a SIMD run half a phase apart (waves
 // 4..7 pass one barrier more at the start): while one reads its fragments
 // and issues the loads, the other keeps the matrix cores busy.  A half tile
 // is refilled as soon as both have read it, one phase later, so a load has
@@ -206,51 +207,65 @@ __device__ __forceinline__ void store4(const GemmParams& P, long long m, long lo
 // CUs busy 1.40 us, held by the power limit (1.8 GHz) and the shared caches.
 // Against all waves in step with one barrier per slice: 5,056 x 28,672 x
 // 4,096 1008 -> 879 us (1.35 PFLOP/s), 4,096 x 4,096 x 16,384 1.49 PFLOP/s.
+// NT = 3 takes 1.10 us per slice, 5 % more per column, and is chosen where its
+// tiles fill the CUs better: 696 x 28,672 x 4,096 (450 tiles in two rounds for
+// 336 in one and a third) 176 -> 154 us, 217 x 37,888 x 3,584 90 -> 81 us.
 // Measured and not taken: four phases per slice of 16 MFMAs (3 % slower),
 // raised wave priority in the MFMA phases (no gain), a third slot for the
 // weights (3 % slower), a K start that differs from workgroup to workgroup
 // (no gain).
+template <int NT>
 __device__ __forceinline__ void tile_256(const GemmParams& P, const Lds& S, int tm, int tn) {
   uint16_t* const As[2][2] = {{S.a0, S.a1}, {S.a2, S.a3}};  // [slice % 2][half tile]
-  uint16_t* const Ws[2][2] = {{S.w0, S.w1}, {S.w2, S.w3}};
+  uint16_t* const Ws[2][2] = {{S.w0, S.w1}, {S.w2, S.w3}};  // [slice % 2][rows 0..127, 128..]
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const long long m0 = (long long)tm * 256, n0 = (long long)tn * 256;
-  const int wn = wave & 3;   // columns 32 wn .. +31 of each half
+  const long long m0 = (long long)tm * 256, n0 = (long long)tn * (64 * NT);
+  const int wn = wave & 3;
+  // this wave's 16-column block nt begins at column 128 (nt / 2) + strip(nt):
+  // two adjacent blocks of each 128 columns, one of a last 64
+  auto strip = [&](int nt) __attribute__((always_inline)) { return nt < 2 || NT == 4 ? 32 * wn + 16 * (nt & 1) : 16 * wn; };
   const int wm = wave >> 2;  // rows 64 wm .. +63 of each half
 
   const uint16_t* a_src[2][2];
-  const uint16_t* w_src[2][2];
+  const uint16_t* w_src[NT];
 #pragma unroll
   for (int h = 0; h < 2; ++h)
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const int row = 16 * wave + 8 * j + (lane >> 3);
-      const int piece = (lane & 7) ^ ((row >> 1) & 7);
-      a_src[h][j] = a_source(P, m0 + 128 * h + row) + 8 * piece;
-      w_src[h][j] = w_source(P, n0 + 128 * h + row) + 8 * piece;
+      a_src[h][j] = a_source(P, m0 + 128 * h + row) + 8 * ((lane & 7) ^ ((row >> 1) & 7));
     }
+#pragma unroll
+  for (int j = 0; j < NT; ++j) {
+    const int row = 64 * j + 8 * wave + (lane >> 3);
+    w_src[j] = w_source(P, n0 + row) + 8 * ((lane & 7) ^ ((row >> 1) & 7));
+  }
   auto load_half = [&](const uint16_t* const (&src)[2], int t, uint16_t* dst) __attribute__((always_inline)) {
 #pragma unroll
     for (int j = 0; j < 2; ++j) load_lds16(src[j] + (long long)t * kBK, dst + (16 * wave + 8 * j) * kBK);
+  };
+  auto load_w = [&](int t, auto bufc) __attribute__((always_inline)) {
+    constexpr int B = decltype(bufc)::value;
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+      load_lds16(w_src[j] + (long long)t * kBK, Ws[B][j >> 1] + (64 * (j & 1) + 8 * wave) * kBK);
   };
 
   const int rl = lane & 15, q = lane >> 4, sw = (rl >> 1) & 7;
   int rd[2];
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks) rd[ks] = rl * kBK + 8 * ((4 * ks + q) ^ sw);
-  f32x4 acc[2][2][2][4];  // [W half][A half][nt][mt]
+  f32x4 acc[NT][2][4];  // [nt][A half][mt]
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt) acc[i][j][nt][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  bf16x8 fa[2][4], fw[2][2][2];  // [ks][mt]; [W half][ks][nt]
+      for (int mt = 0; mt < 4; ++mt) acc[nt][h][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  bf16x8 fa[2][4], fw[2][NT];  // [ks][mt], [ks][nt]
   auto read_a = [&](const uint16_t* base) __attribute__((always_inline)) {
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks)
@@ -258,24 +273,21 @@ __device__ __forceinline__ void tile_256(const GemmParams& P, const Lds& S, int 
       for (int mt = 0; mt < 4; ++mt)
         fa[ks][mt] = as_bf16x8(*reinterpret_cast<const uint4*>(base + (64 * wm + 16 * mt) * kBK + rd[ks]));
   };
-  auto read_w = [&](const uint16_t* base, int h) __attribute__((always_inline)) {
+  auto read_w = [&](auto bufc, int nt) __attribute__((always_inline)) {
+    constexpr int B = decltype(bufc)::value;
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt)
-        fw[h][ks][nt] = as_bf16x8(*reinterpret_cast<const uint4*>(base + (32 * wn + 16 * nt) * kBK + rd[ks]));
+      fw[ks][nt] = as_bf16x8(*reinterpret_cast<const uint4*>(Ws[B][nt >> 1] + strip(nt) * kBK + rd[ks]));
   };
-  auto multiply = [&](int ah) __attribute__((always_inline)) {
+  auto multiply = [&](int h) __attribute__((always_inline)) {
     barrier_only();
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-      for (int wh = 0; wh < 2; ++wh)
+      for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-          for (int mt = 0; mt < 4; ++mt)
-            acc[wh][ah][nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[wh][ks][nt], fa[ks][mt], acc[wh][ah][nt][mt], 0, 0, 0);
+        for (int mt = 0; mt < 4; ++mt)
+          acc[nt][h][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[ks][nt], fa[ks][mt], acc[nt][h][mt], 0, 0, 0);
     barrier_only();
   };
 
@@ -289,20 +301,21 @@ __device__ __forceinline__ void tile_256(const GemmParams& P, const Lds& S, int 
     // upper rows.  The waits leave the loads issued after the half tiles of
     // the next phase in flight, and finish this wave's reads before the
     // barrier, after which others may refill what it read.
-    read_w(Ws[B][0], 0);
+    read_w(bufc, 0);
+    read_w(bufc, 1);
     read_a(As[B][0]);
-    read_w(Ws[B][1], 1);
+#pragma unroll
+    for (int nt = 2; nt < NT; ++nt) read_w(bufc, nt);
     if constexpr (MORE >= 1) load_half(a_src[1], t + 1, As[1 - B][1]);
-    __builtin_amdgcn_s_waitcnt(wait_imm(MORE >= 1 ? 8 : 0, 0));
+    __builtin_amdgcn_s_waitcnt(wait_imm(MORE >= 1 ? 4 + NT : 0, 0));
     multiply(0);
     // lower rows
     read_a(As[B][1]);
     if constexpr (MORE >= 2) {
       load_half(a_src[0], t + 2, As[B][0]);
-      load_half(w_src[0], t + 2, Ws[B][0]);
-      load_half(w_src[1], t + 2, Ws[B][1]);
+      load_w(t + 2, bufc);
     }
-    __builtin_amdgcn_s_waitcnt(wait_imm(MORE >= 2 ? 8 : MORE == 1 ? 2 : 0, 0));
+    __builtin_amdgcn_s_waitcnt(wait_imm(MORE >= 2 ? 4 + NT : MORE == 1 ? 2 : 0, 0));
     multiply(1);
   };
 
@@ -311,13 +324,11 @@ __device__ __forceinline__ void tile_256(const GemmParams& P, const Lds& S, int 
     constexpr int B = decltype(bufc)::value;
     const int second = min(1, nk - 1);  // a single slice is loaded twice
     load_half(a_src[0], 0, As[B][0]);
-    load_half(w_src[0], 0, Ws[B][0]);
-    load_half(w_src[1], 0, Ws[B][1]);
+    load_w(0, bufc);
     load_half(a_src[1], 0, As[B][1]);
     load_half(a_src[0], second, As[1 - B][0]);
-    load_half(w_src[0], second, Ws[1 - B][0]);
-    load_half(w_src[1], second, Ws[1 - B][1]);
-    __builtin_amdgcn_s_waitcnt(wait_imm(8, 15));
+    load_w(second, Int<1 - B>{});
+    __builtin_amdgcn_s_waitcnt(wait_imm(4 + NT, 15));
     barrier_only();
     if (wm == 1) barrier_only();
   };
@@ -342,26 +353,22 @@ __device__ __forceinline__ void tile_256(const GemmParams& P, const Lds& S, int 
   if (wm == 0) barrier_only();
 
 #pragma unroll
-  for (int ah = 0; ah < 2; ++ah) {
-    const long long m = m0 + 128 * ah + 64 * wm + rl;
-    const long long n = n0 + 32 * wn + 4 * q;
-    uint2 r[4][2][2];
+  for (int h = 0; h < 2; ++h) {
+    const long long m = m0 + 128 * h + 64 * wm + rl;
+    const long long n = n0 + 4 * q;
+    uint2 r[4][NT];
     bool zero[4];
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt) {
       zero[mt] = zero_row(P, m + 16 * mt);
 #pragma unroll
-      for (int wh = 0; wh < 2; ++wh)
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt) r[mt][wh][nt] = residual4(P, m + 16 * mt, n + 128 * wh + 16 * nt);
+      for (int nt = 0; nt < NT; ++nt) r[mt][nt] = residual4(P, m + 16 * mt, n + 128 * (nt >> 1) + strip(nt));
     }
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
-      for (int wh = 0; wh < 2; ++wh)
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
-          store4(P, m + 16 * mt, n + 128 * wh + 16 * nt, zero[mt], acc[wh][ah][nt][mt], r[mt][wh][nt]);
+      for (int nt = 0; nt < NT; ++nt)
+        store4(P, m + 16 * mt, n + 128 * (nt >> 1) + strip(nt), zero[mt], acc[nt][h][mt], r[mt][nt]);
   }
 }
 
@@ -372,8 +379,8 @@ __device__ __forceinline__ void tile_256(const GemmParams& P, const Lds& S, int 
 // CU.  One barrier per slice; each wave reads the fragments of the next slice
 // between the MFMAs of this one.  At the end the groups' float32 sums are
 // added through LDS in a fixed order.  With all CUs busy 64 of K take
-// 0.53 us (128) or 0.24 us (64): a 128 tile runs at 66 % and a 64 tile at
-// 36 % of the rate of a 256 tile, bound by the loads (64 and 128 bytes per
+// 0.48 us (128) or 0.23 us (64): a 128 tile runs at 73 % and a 64 tile at
+// 38 % of the rate of a 256 tile, bound by the loads (64 and 128 bytes per
 // CU and MFMA cycle).  Against 256 x 256 tiles only: 217 x 3,584 x 18,944
 // 428 -> 72 us, 696 x 4,096 x 4,096 94 -> 30 us, 696 x 4,096 x 14,336 316 ->
 // 107 us, and with both sizes in one launch 5,056 x 4,096 x 14,336 692 ->
@@ -589,9 +596,9 @@ __device__ __forceinline__ void tile_ring(const GemmParams& P, const Lds& L, lon
 }
 
 // One tile of the launch: a large one for the first big_wgs workgroups, a
-// small one for the others.  TOP: large tiles are 256 and small ones 128
-// wide; otherwise 128 and 64.
-template <bool TOP>
+// small one for the others.  MODE 0: 256 x 256 and 128 x 128, 1: 256 x 192
+// and 128 x 128, 2: 128 x 128 and 64 x 64.
+template <int MODE>
 __global__ __launch_bounds__(kThreads) void gemm_kernel(const GemmParams P) {
   __shared__ __attribute__((aligned(16))) uint16_t A0[kArray], A1[kArray], A2[kArray], A3[kArray];
   __shared__ __attribute__((aligned(16))) uint16_t W0[kArray], W1[kArray], W2[kArray], W3[kArray];
@@ -599,11 +606,12 @@ __global__ __launch_bounds__(kThreads) void gemm_kernel(const GemmParams P) {
   int tm, tn;
   if ((int)blockIdx.x < P.big_wgs) {
     tile_of((int)blockIdx.x, P.big_tiles_m, P.big_tiles_n, tm, tn);
-    if constexpr (TOP) tile_256(P, S, tm, tn);
+    if constexpr (MODE == 0) tile_256<4>(P, S, tm, tn);
+    else if constexpr (MODE == 1) tile_256<3>(P, S, tm, tn);
     else tile_ring<128, 2, 2, 2>(P, S, (long long)tm * 128, tn);
   } else {
     tile_of((int)blockIdx.x - P.big_wgs, P.small_tiles_m, P.small_tiles_n, tm, tn);
-    if constexpr (TOP) tile_ring<128, 2, 2, 2>(P, S, P.small_row0 + (long long)tm * 128, tn);
+    if constexpr (MODE < 2) tile_ring<128, 2, 2, 2>(P, S, P.small_row0 + (long long)tm * 128, tn);
     else tile_ring<64, 2, 1, 4>(P, S, P.small_row0 + (long long)tm * 64, tn);
   }
 }
@@ -611,14 +619,16 @@ __global__ __launch_bounds__(kThreads) void gemm_kernel(const GemmParams P) {
 // ---- choice of tiles -----------------------------------------------------------
 // Measured time of a tile with all CUs busy, in ns: per 64 of K, and once per
 // tile (first loads, last sums and stores).  On 50 shapes of 90 to 14,000
-// rows the split these choose was within 1.1 % (geometric mean) of the best of
+// rows the split these choose was within 2 % (geometric mean) of the best of
 // the splits tried.
 struct TileCost {
-  int width;
+  int rows, cols;
   long long slice_ns, fixed_ns;
   long long of(long long k) const { return slice_ns * (k / kBK) + fixed_ns; }
 };
-constexpr TileCost kCost256 = {256, 1400, 8000}, kCost128 = {128, 530, 1000}, kCost64 = {64, 240, 1500};
+// large and small tiles of each mode
+constexpr TileCost kBig[3] = {{256, 256, 1400, 8000}, {256, 192, 1100, 7000}, {128, 128, 480, 1500}};
+constexpr TileCost kSmall[3] = {{128, 128, 480, 1500}, {128, 128, 480, 1500}, {64, 64, 230, 1500}};
 constexpr long long kCus = 256;
 
 long long div_up(long long a, long long b) { return (a + b - 1) / b; }
@@ -642,29 +652,29 @@ long long makespan(long long big, long long cb, long long small, long long cs) {
 }
 
 struct GemmPlan {
-  bool top;              // 256/128 tiles, otherwise 128/64
-  long long big_rows;    // row tiles of the larger size
+  int mode;
+  long long big_rows;  // row tiles of the larger size
 };
 
-// The split of the rows into large and small tiles with the shortest
-// estimated time.  Only the last rows are worth small tiles: as many as one
-// round of large ones covers.
+// The tiles, and the split of the rows into large and small ones, with the
+// shortest estimated time.  Only the last rows are worth small tiles: as many
+// as one round of large ones covers.
 GemmPlan plan_of(long long m, long long n, long long k) {
-  GemmPlan best = {true, div_up(m, 256)};
+  GemmPlan best = {0, div_up(m, 256)};
   long long best_t = -1;
-  for (int top = 1; top >= 0; --top) {
-    const TileCost& B = top ? kCost256 : kCost128;
-    const TileCost& S = top ? kCost128 : kCost64;
-    const long long all = div_up(m, B.width), cols = div_up(n, B.width), scols = div_up(n, S.width);
+  for (int mode = 0; mode < 3; ++mode) {
+    const TileCost& B = kBig[mode];
+    const TileCost& S = kSmall[mode];
+    const long long all = div_up(m, B.rows), cols = div_up(n, B.cols), scols = div_up(n, S.cols);
     const long long window = div_up(kCus, cols) + 1;
     for (long long r = all; r >= 0 && r >= all - window; --r) {
-      const long long rest = r == all ? 0 : m - r * B.width;
-      const long long big = r * cols, small = div_up(rest, S.width) * scols;
+      const long long rest = r == all ? 0 : m - r * B.rows;
+      const long long big = r * cols, small = div_up(rest, S.rows) * scols;
       if (big + small > (long long)UINT32_MAX / kThreads) continue;
       const long long t = makespan(big, B.of(k), small, S.of(k));
       if (best_t < 0 || t < best_t) {
         best_t = t;
-        best = {top != 0, r};
+        best = {mode, r};
       }
     }
   }
@@ -693,16 +703,18 @@ hipError_t launch_gemm(int64_t m, int64_t n, int64_t k, const uint16_t* a, int64
   P.n = n;
   P.k = k;
   const GemmPlan plan = plan_of(m, n, k);
-  const int bw = plan.top ? 256 : 128, sw = bw / 2;
+  const TileCost& B = kBig[plan.mode];
+  const TileCost& S = kSmall[plan.mode];
   P.big_tiles_m = (int)plan.big_rows;
-  P.big_tiles_n = (int)div_up(n, bw);
+  P.big_tiles_n = (int)div_up(n, B.cols);
   P.big_wgs = P.big_tiles_m * P.big_tiles_n;
-  P.small_row0 = plan.big_rows * bw;
-  P.small_tiles_m = P.small_row0 < m ? (int)div_up(m - P.small_row0, sw) : 0;
-  P.small_tiles_n = (int)div_up(n, sw);
+  P.small_row0 = plan.big_rows * B.rows;
+  P.small_tiles_m = P.small_row0 < m ? (int)div_up(m - P.small_row0, S.rows) : 0;
+  P.small_tiles_n = (int)div_up(n, S.cols);
   const unsigned wgs = (unsigned)P.big_wgs + (unsigned)P.small_tiles_m * (unsigned)P.small_tiles_n;
-  if (plan.top) hipLaunchKernelGGL(gemm_kernel<true>, dim3(wgs), dim3(kThreads), 0, s, P);
-  else hipLaunchKernelGGL(gemm_kernel<false>, dim3(wgs), dim3(kThreads), 0, s, P);
+  if (plan.mode == 0) hipLaunchKernelGGL(gemm_kernel<0>, dim3(wgs), dim3(kThreads), 0, s, P);
+  else if (plan.mode == 1) hipLaunchKernelGGL(gemm_kernel<1>, dim3(wgs), dim3(kThreads), 0, s, P);
+  else hipLaunchKernelGGL(gemm_kernel<2>, dim3(wgs), dim3(kThreads), 0, s, P);
   return hipGetLastError();
 }
 
