@@ -7,7 +7,7 @@
 //   * the split of the fused Q/K/V projection output into Q, K and V with
 //     RoPE applied to Q and K at each token's position;
 //   * the gated SiLU of the feed-forward block.
-// The projections themselves are plain GEMMs left to a GEMM library.
+// The projections between them are in gemm.hip.
 //
 // All three kernels are bound by HBM bandwidth: each reads its input once
 // and writes its output once, in 16-byte vectors.  Outputs use ordinary
