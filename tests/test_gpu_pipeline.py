@@ -242,3 +242,38 @@ def test_stage_layer_many_fragments(K, kind):
         (torch.randn(1 << 20, device="cuda:0") * 2).sum().item()   # unrelated eager work
         g.replay()
         check()
+
+
+def test_stage_layer_pinned_source_rewritten(K):
+    """The fragments' pinned buffer is filled again for the next layer, as a
+    loader does: every call (and every replay) takes what it holds then."""
+    n, rows, re = 300, 8, 2 * 128
+    w = W.Workload("rewritten", (rows,) * n, 0, 8, 2)
+    L, plan = _layout_plan(K, w, zero=False)
+    host = torch.zeros((2, n, rows + 1, re), dtype=torch.int16).pin_memory()   # a row between fragments
+    ptrs = [[host[t, i].data_ptr() for i in range(n)] for t in range(2)]
+    kc = torch.zeros((n * rows, 2, 128), dtype=torch.int16, device="cuda:0")
+    vc, want_k = torch.zeros_like(kc), torch.zeros_like(kc)
+    gen = torch.Generator().manual_seed(4)
+
+    def fill():
+        torch.cuda.synchronize()
+        host.copy_(torch.randint(0, 2 ** 14, host.shape, generator=gen, dtype=torch.int16))
+
+    def check():
+        torch.cuda.synchronize()
+        K.kvc_rope_shift(L, plan, host[0, :, :rows].contiguous().cuda(), want_k)
+        assert torch.equal(vc.cpu().reshape(n, rows, re), host[1, :, :rows])
+        assert torch.equal(kc, want_k)
+
+    for _ in range(3):
+        fill()
+        K.kvc_stage_layer(L, plan, ptrs[0], ptrs[1], kc, vc)
+        check()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        K.kvc_stage_layer(L, plan, ptrs[0], ptrs[1], kc, vc)
+    for _ in range(3):
+        fill()
+        g.replay()
+        check()
