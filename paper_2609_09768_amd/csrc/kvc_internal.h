@@ -67,6 +67,7 @@ inline int64_t topk_blocks(int64_t n) { return (n + kTopkRowsPerBlock - 1) / kTo
 // State of the fused selection (one launch for all steps, grid barriers),
 // zero at its start: three rotating histograms, the barrier's arrival
 // counter, the range of the keys and the candidates' count.
+constexpr int kTopkMaxLevels = 8;  // histograms of 256 bins that 64-bit keys can take
 struct TopkFused {
   unsigned int hist[3][256];
   unsigned int arrive;
@@ -99,9 +100,13 @@ hipError_t launch_shift_deviation(const void* plan, uint64_t layout_hash, int n_
                                   hipStream_t s);
 // Bytes at the start of the selection's workspace to be zero when it starts.
 size_t topk_clear_bytes(int64_t n);
-// cleared: they are; otherwise a launch of its own does it.
+// cleared: they are; otherwise a launch of its own does it.  spin_limit: looks
+// at the arrival counter before a wait of the selection's grid barriers is
+// given up (the default takes seconds).
+constexpr int kTopkSpinLimit = 1 << 22;
 hipError_t launch_select_topk(const double* dev, int64_t n, int64_t k, int64_t n_append,
-                              int32_t* idx_out, void* ws, bool cleared, hipStream_t s);
+                              int32_t* idx_out, void* ws, bool cleared, hipStream_t s,
+                              int spin_limit = kTopkSpinLimit);
 hipError_t launch_scatter_rows(const int32_t* sel, int64_t n_sel, int compact,
                                const uint16_t* k_fresh, const uint16_t* v_fresh,
                                int64_t n_fresh, uint16_t* k_cache, uint16_t* v_cache,

@@ -392,12 +392,20 @@ hipError_t launch_small(const double* dev, int64_t n, int64_t k, int64_t n_appen
 constexpr int kFusedMaxBlocks = 128;
 constexpr long long kFusedMaxRows = (long long)kFusedMaxBlocks * kTopkRowsPerBlock;
 constexpr int kFusedWaves = kThreads / 64;
-// A bound on every barrier wait (seconds), so that no wait is endless: it is
-// reached only if some workgroup of the grid cannot run at all, which at
-// most 128 workgroups of 256 threads on 256 CUs does not happen (the other
-// kernels that may share the GPU, on other streams, all finish on their
-// own); the selection would then be wrong.
-constexpr int kSpinLimit = 1 << 22;
+// Every barrier wait is bounded (spin_limit looks at the counter, seconds in
+// all), and a workgroup whose wait runs out leaves the kernel: it reads no
+// exchanged value, and since it does not arrive again, no later barrier lets
+// any other workgroup pass.  So whoever goes on has seen every arrival and
+// holds the same bracket as the others, and the launch ends after one
+// exhausted wait per workgroup at most, with the rows of the workgroups that
+// left not written.  It happens only if some workgroup of the grid cannot run
+// at all, which at most 128 workgroups of 256 threads on 256 CUs does not
+// (the other kernels that may share the GPU, on other streams, all finish on
+// their own).
+// The search needs at most eight histograms of 256 bins for 64-bit keys.
+// That, and the number of candidates, is checked all the same, so that a
+// workspace which another stream writes meanwhile (not allowed) makes the
+// selection wrong and nothing else.
 static_assert(sizeof(TopkFused::hist[0]) == kThreads * 4 && kMaxCand * 8 <= kThreads * 4, "candidates fit a histogram");
 
 __global__ __launch_bounds__(kThreads) void topk_fused_init(TopkFused* st) {
@@ -412,30 +420,35 @@ __device__ __forceinline__ void store_dev(unsigned int* p, unsigned int v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Every workgroup of the grid arrives once per barrier id; returns when all
-// have arrived at barrier id (or the spin bound is reached).  Everything the
+// Every workgroup of the grid arrives once per barrier id; true, for the
+// whole workgroup, when all have arrived at barrier id, false when the spin
+// bound was reached before that.  `seen` is the workgroup's.  Everything the
 // workgroups exchange (histogram adds and clears, the range, block counts,
 // candidates, the arrival counter) is a device-scope atomic, performed where
 // all XCDs see it, so the barrier needs no cache writeback: each wave waits
 // until its own atomics are done before the workgroup arrives, and a
 // workgroup reads the exchanged values only after it has seen every arrival.
-__device__ __forceinline__ void grid_barrier(TopkFused* st, unsigned int id) {
+__device__ __forceinline__ bool grid_barrier(TopkFused* st, unsigned int id, int spin_limit, int* seen) {
   __builtin_amdgcn_s_waitcnt(0);  // this wave's adds and stores are done
   __syncthreads();
   if (threadIdx.x == 0) {
     __hip_atomic_fetch_add(&st->arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const unsigned int target = (id + 1u) * gridDim.x;
-    for (int it = 0; it < kSpinLimit; ++it) {
-      if (load_dev(&st->arrive) >= target) break;
-      __builtin_amdgcn_s_sleep(1);
+    int all = 0;
+    for (int it = 0; it < spin_limit && !all; ++it) {
+      all = load_dev(&st->arrive) >= target;
+      if (!all) __builtin_amdgcn_s_sleep(1);
     }
+    *seen = all;
   }
   __syncthreads();
+  return *seen != 0;
 }
 
 __global__ __launch_bounds__(kThreads) void topk_fused(const double* __restrict__ dev, long long n, long long k,
                                                        long long n_append, TopkFused* st,
-                                                       unsigned int* __restrict__ bc, int32_t* __restrict__ out) {
+                                                       unsigned int* __restrict__ bc, int32_t* __restrict__ out,
+                                                       int spin_limit) {
   __shared__ unsigned int h[kThreads];
   __shared__ unsigned int wsum[kFusedWaves];
   __shared__ unsigned long long smax[kFusedWaves], sneg[kFusedWaves];
@@ -443,6 +456,7 @@ __global__ __launch_bounds__(kThreads) void topk_fused(const double* __restrict_
   __shared__ int cr[kMaxCand];
   __shared__ Bracket s_next;
   __shared__ unsigned int red[2];
+  __shared__ int seen;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const long long base = (long long)blockIdx.x * kTopkRowsPerBlock + (long long)t * kItems;
   for (long long i = (long long)blockIdx.x * kThreads + t; i < n_append; i += (long long)gridDim.x * kThreads)
@@ -476,12 +490,13 @@ __global__ __launch_bounds__(kThreads) void topk_fused(const double* __restrict_
     __hip_atomic_fetch_max(&st->max_not, neg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   unsigned int bar = 0u;
-  grid_barrier(st, bar++);
+  if (!grid_barrier(st, bar++, spin_limit, &seen)) return;
   hi = __hip_atomic_load(&st->max_key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   neg = __hip_atomic_load(&st->max_not, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   Bracket b = {~neg, span_bits(~neg, hi), k, (unsigned int)n};
+  if (t == 0) s_next = b;
   int level = 0;
-  while (!b.done()) {
+  while (level < kTopkMaxLevels && !b.done()) {
     const int shift = b.bits > 8 ? b.bits - 8 : 0;
     unsigned int* gh = st->hist[level % 3];
 #pragma unroll
@@ -490,7 +505,7 @@ __global__ __launch_bounds__(kThreads) void topk_fused(const double* __restrict_
     __syncthreads();
     if (h[t]) atomicAdd(&gh[t], h[t]);
     h[t] = 0u;
-    grid_barrier(st, bar++);
+    if (!grid_barrier(st, bar++, spin_limit, &seen)) return;
     const unsigned int c = load_dev(&gh[t]);
     unsigned int tot;
     const unsigned int before = block_scan<kFusedWaves>(c, wsum, tot);
@@ -525,6 +540,7 @@ __global__ __launch_bounds__(kThreads) void topk_fused(const double* __restrict_
     for (int i = 0; i < kItems; ++i)
       if (in >> i & 1u) {
         const unsigned int j = atomicAdd(&st->cand, 1u);
+        if (j >= kMaxCand) continue;
         __hip_atomic_store(&gk[j], key[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         store_dev(&gr[j], (unsigned int)(base + i));
       }
@@ -535,7 +551,7 @@ __global__ __launch_bounds__(kThreads) void topk_fused(const double* __restrict_
     red[0] = 0u;
     red[1] = 0u;
   }
-  grid_barrier(st, bar++);
+  if (!grid_barrier(st, bar++, spin_limit, &seen)) return;
   if (t < (int)blockIdx.x) {  // at most 128 workgroups
     atomicAdd(&red[0], load_dev(&bc[2 * t]));
     if (ties) atomicAdd(&red[1], load_dev(&bc[2 * t + 1]));
@@ -590,7 +606,7 @@ hipError_t launch_iota(int32_t* out, long long count, long long start, hipStream
 size_t topk_clear_bytes(int64_t n) { return n > kSmallMax && n <= kFusedMaxRows ? sizeof(TopkFused) : 0; }
 
 hipError_t launch_select_topk(const double* dev, int64_t n, int64_t k, int64_t n_append,
-                              int32_t* idx_out, void* ws, bool cleared, hipStream_t s) {
+                              int32_t* idx_out, void* ws, bool cleared, hipStream_t s, int spin_limit) {
   if (k == 0) return launch_iota(idx_out, n_append, n, s);
   if (k == n) return launch_iota(idx_out, n + n_append, 0, s);
   if (n <= kSmallMax) {
@@ -607,7 +623,7 @@ hipError_t launch_select_topk(const double* dev, int64_t n, int64_t k, int64_t n
     TopkFused* fs = static_cast<TopkFused*>(ws);
     if (!cleared) hipLaunchKernelGGL(topk_fused_init, dim3(1), dim3(kThreads), 0, s, fs);
     hipLaunchKernelGGL(topk_fused, dim3((unsigned)nblk), dim3(kThreads), 0, s, dev, (long long)n, (long long)k,
-                       (long long)n_append, fs, bc, idx_out);
+                       (long long)n_append, fs, bc, idx_out, spin_limit);
     return hipGetLastError();
   }
   TopkState* st = static_cast<TopkState*>(ws);

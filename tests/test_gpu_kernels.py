@@ -5,6 +5,8 @@ adjusted keys and deviations are compared bit-exactly too (both sides round
 once from float64); attention outputs within 2e-2 abs + 1e-2 rel.
 """
 
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -383,6 +385,42 @@ def test_select_topk_brackets(K, n):
     for d in (wide, some, np.abs(wide)):
         for k in (1, n // 7 + 1, n // 2, n - 1):
             assert np.array_equal(_topk_gpu(K, d, k), oracle.select_topk(d, k)), k
+
+
+# The library's own launcher with a limit on the grid barriers' waits so small
+# that they run out, at the first barrier or a later one, in some workgroups
+# or in all: the launch ends, writes nothing outside its buffers, and what it
+# writes of the selection is right; the workspace then serves the next call.
+@pytest.mark.parametrize("n", [16385, 34816, 262144])
+def test_select_topk_barrier_waits_given_up(K, n):
+    f = ctypes.CDLL(K.LIB_PATH)._ZN3kvc18launch_select_topkEPKdlllPiPvbP12ihipStream_ti
+    f.restype = ctypes.c_int
+    i64, vp = ctypes.c_int64, ctypes.c_void_p
+    f.argtypes = [vp, i64, i64, i64, vp, vp, ctypes.c_bool, vp, ctypes.c_int]
+    rng = np.random.default_rng(n)
+    wide = rng.integers(0, 2 ** 64, n, dtype=np.uint64).view(np.float64).copy()   # eight histograms
+    wide[~np.isfinite(wide)] = 0.0
+    k, n_append, g = n // 7, 5, 512
+    ws_bytes = (K.kvc_select_topk_workspace(n) + 255) // 256 * 256
+    stream = torch.cuda.current_stream().cuda_stream
+    for d in (wide, rng.random(n), rng.integers(0, 3, n).astype(np.float64)):
+        want = np.concatenate([oracle.select_topk(d, k), np.arange(n, n + n_append)])
+        dev = up(d)
+        ws = torch.full((ws_bytes + 2 * g,), 0x5A, dtype=torch.uint8, device="cuda:0")
+        for limit in (0, 1, 2, 4, 8, 16, 32, 64, 128, 256, 1 << 22):
+            out = torch.full((g + k + n_append + g,), -7, dtype=torch.int32, device="cuda:0")
+            print(f"n={n} limit={limit}", flush=True)
+            assert f(dev.data_ptr(), n, k, n_append, out.data_ptr() + 4 * g, ws.data_ptr() + g, False, stream, limit) == 0
+            torch.cuda.synchronize()
+            got = out.cpu().numpy()
+            assert (got[:g] == -7).all() and (got[g + k + n_append:] == -7).all(), limit
+            assert (ws[:g] == 0x5A).all() and (ws[g + ws_bytes:] == 0x5A).all(), limit
+            got = got[g:g + k + n_append]
+            assert ((got == want) | (got == -7)).all(), limit
+            assert np.array_equal(got[k:], want[k:]), limit     # the appended rows wait for nothing
+            if limit == 0:
+                assert (got[:k] == -7).all()
+        assert np.array_equal(got, want)
 
 
 @pytest.mark.parametrize("m", [3000, 12000, 20000])
