@@ -275,7 +275,7 @@ hipError_t shift_and_select(const kvc_layout* L, const LayoutInfo& li, const kvc
   double* dev = static_cast<double*>(ws);
   void* tws = select ? static_cast<char*>(ws) + kvc::align256(sizeof(double) * (size_t)li.n_reused) : nullptr;
   if (select && k_src && kvc::shift_deviation_fits(li.n_reused, hkv)) {
-    e = kvc::launch_shift_deviation(plan->device, plan->layout_id, L->n_chunks, li.n_tiles, hkv,
+    e = kvc::launch_shift_deviation(plan->device, plan->layout_id, L->n_chunks, li.n_tiles, li.n_reused, hkv,
                                     static_cast<const uint16_t*>(k_src), static_cast<uint16_t*>(k_cache),
                                     static_cast<const uint16_t*>(k_fresh), dev, s);
     if (e != hipSuccess) return e;

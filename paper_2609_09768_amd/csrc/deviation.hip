@@ -375,19 +375,27 @@ template <int WAVES, int LPR, int UPL>
 __global__ __launch_bounds__(64 * WAVES) void shift_deviation_kernel(
     const PlanHeader* __restrict__ hdr, const ShiftTile* __restrict__ tiles, uint64_t layout_hash,
     const uint16_t* src /* may equal dst */, uint16_t* dst, const uint16_t* __restrict__ kf, double* __restrict__ dev,
-    int in_place, const double2* __restrict__ rot_table) {
+    int64_t n_rows, int in_place, const double2* __restrict__ rot_table) {
   constexpr int kRpw = 64 / LPR;
   constexpr int kRowElems = LPR * UPL * 16;
   constexpr int kPieces = 2 * LPR * UPL;
   __shared__ unsigned long long sacc[WAVES][kRpw][kDigits];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int sub = lane / LPR, p = lane % LPR, jg = p & 7;
-  const ShiftTile t = tiles[blockIdx.x];
-  // a plan buffer overwritten since its descriptor was made is not used
-  if ((hdr->layout_hash != layout_hash) | (t.row_end < t.row_begin) | (t.chunk < 0) |
-      (t.flags > (kTileDeltaZero | kTileZeroKv)))
+  ShiftTile t = tiles[blockIdx.x];
+  // a plan buffer overwritten since its descriptor was made is not used: the
+  // keys stay as they are in dst, and the workgroups share their rows evenly
+  // for the deviation, which every row must get
+  const bool stale = hdr->layout_hash != layout_hash;
+  if (stale) {
+    t.chunk = 0;
+    t.row_begin = (int32_t)(n_rows * blockIdx.x / gridDim.x);
+    t.row_end = (int32_t)(n_rows * (blockIdx.x + 1) / gridDim.x);
+    src = dst;
+  } else if ((t.row_end < t.row_begin) | (t.chunk < 0) | (t.flags > (kTileDeltaZero | kTileZeroKv))) {
     return;
-  const bool keep = in_place && (t.flags & kTileDeltaZero);
+  }
+  const bool keep = stale || (in_place && (t.flags & kTileDeltaZero));
   double c[8], s[8];
   const double2* rot = rot_table + (size_t)t.chunk * kHalf + jg * 8;
 #pragma unroll
@@ -444,12 +452,12 @@ __global__ __launch_bounds__(64 * WAVES) void shift_deviation_kernel(
 }
 
 template <int WAVES, int LPR, int UPL>
-hipError_t launch_shift_dev(const char* plan, uint64_t layout_hash, int n_chunks, int n_tiles, const uint16_t* src,
-                            uint16_t* dst, const uint16_t* kf, double* dev, hipStream_t s) {
+hipError_t launch_shift_dev(const char* plan, uint64_t layout_hash, int n_chunks, int n_tiles, int64_t n_rows,
+                            const uint16_t* src, uint16_t* dst, const uint16_t* kf, double* dev, hipStream_t s) {
   hipLaunchKernelGGL((shift_deviation_kernel<WAVES, LPR, UPL>), dim3((unsigned)n_tiles), dim3(64 * WAVES), 0, s,
                      reinterpret_cast<const PlanHeader*>(plan),
                      reinterpret_cast<const ShiftTile*>(plan + plan_tile_offset(n_chunks)), layout_hash, src, dst, kf,
-                     dev, (int)(src == dst), reinterpret_cast<const double2*>(plan + plan_rot_offset()));
+                     dev, n_rows, (int)(src == dst), reinterpret_cast<const double2*>(plan + plan_rot_offset()));
   return hipGetLastError();
 }
 
@@ -483,15 +491,15 @@ bool shift_deviation_fits(int64_t n_reused, int n_kv_heads) {
          (n_kv_heads == 1 || n_kv_heads == 2 || n_kv_heads == 4 || n_kv_heads == 8);
 }
 
-hipError_t launch_shift_deviation(const void* plan, uint64_t layout_hash, int n_chunks, int n_tiles, int n_kv_heads,
-                                  const uint16_t* k_src, uint16_t* k_dst, const uint16_t* k_fresh, double* dev,
-                                  hipStream_t s) {
+hipError_t launch_shift_deviation(const void* plan, uint64_t layout_hash, int n_chunks, int n_tiles, int64_t n_reused,
+                                  int n_kv_heads, const uint16_t* k_src, uint16_t* k_dst,
+                                  const uint16_t* k_fresh, double* dev, hipStream_t s) {
   const char* p = static_cast<const char*>(plan);
   switch (n_kv_heads) {  // 16 rows in one pass of the workgroup
-    case 1: return launch_shift_dev<2, 8, 1>(p, layout_hash, n_chunks, n_tiles, k_src, k_dst, k_fresh, dev, s);
-    case 2: return launch_shift_dev<4, 16, 1>(p, layout_hash, n_chunks, n_tiles, k_src, k_dst, k_fresh, dev, s);
-    case 4: return launch_shift_dev<4, 16, 2>(p, layout_hash, n_chunks, n_tiles, k_src, k_dst, k_fresh, dev, s);
-    default: return launch_shift_dev<8, 32, 2>(p, layout_hash, n_chunks, n_tiles, k_src, k_dst, k_fresh, dev, s);
+    case 1: return launch_shift_dev<2, 8, 1>(p, layout_hash, n_chunks, n_tiles, n_reused, k_src, k_dst, k_fresh, dev, s);
+    case 2: return launch_shift_dev<4, 16, 1>(p, layout_hash, n_chunks, n_tiles, n_reused, k_src, k_dst, k_fresh, dev, s);
+    case 4: return launch_shift_dev<4, 16, 2>(p, layout_hash, n_chunks, n_tiles, n_reused, k_src, k_dst, k_fresh, dev, s);
+    default: return launch_shift_dev<8, 32, 2>(p, layout_hash, n_chunks, n_tiles, n_reused, k_src, k_dst, k_fresh, dev, s);
   }
 }
 

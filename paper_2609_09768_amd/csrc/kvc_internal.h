@@ -32,7 +32,7 @@ constexpr int64_t kMaxGrid = int64_t(1) << 20;
 // passes them to the kernel with n_tiles and only the header's hash and the
 // tile itself are read before the data.
 struct PlanHeader {
-  uint64_t layout_hash;  // checked by the kernel: a stale plan does nothing
+  uint64_t layout_hash;  // checked by the kernels: a stale plan adjusts nothing
   int32_t n_chunks;
   int32_t n_tiles;
   int64_t n_reused;
@@ -95,9 +95,9 @@ hipError_t launch_kv_deviation(int64_t n_rows, int n_kv_heads, const uint16_t* k
                                hipStream_t s);
 // Adjustment and deviation in one launch, for the small requests it fits.
 bool shift_deviation_fits(int64_t n_reused, int n_kv_heads);
-hipError_t launch_shift_deviation(const void* plan, uint64_t layout_hash, int n_chunks, int n_tiles, int n_kv_heads,
-                                  const uint16_t* k_src, uint16_t* k_dst, const uint16_t* k_fresh, double* dev,
-                                  hipStream_t s);
+hipError_t launch_shift_deviation(const void* plan, uint64_t layout_hash, int n_chunks, int n_tiles, int64_t n_reused,
+                                  int n_kv_heads, const uint16_t* k_src, uint16_t* k_dst,
+                                  const uint16_t* k_fresh, double* dev, hipStream_t s);
 // Bytes at the start of the selection's workspace to be zero when it starts.
 size_t topk_clear_bytes(int64_t n);
 // cleared: they are; otherwise a launch of its own does it.  spin_limit: looks

@@ -312,3 +312,36 @@ def test_select_tokens_small_requests(K, n_kv_heads, lens, in_place):
         assert np.array_equal(got[k:], np.arange(n_r, n_r + n_q))
         if k == len(big) // 2:
             assert np.array_equal(got[:k], big[1::2])
+
+
+@pytest.mark.parametrize("in_place", [False, True])
+@pytest.mark.parametrize("n_kv_heads,lens", [(1, (300, 2, 41)), (2, (17, 300, 5)), (4, (64, 31, 2)), (8, (250, 3, 16, 90)),
+                                             (3, (40, 60)), (8, (9000, 8001))])
+def test_select_tokens_overwritten_plan(K, n_kv_heads, lens, in_place):
+    """A plan buffer overwritten after its upload adjusts nothing, and the
+    selection goes by the deviations of the keys as they are, whether the
+    request takes the one launch of the small ones (1, 2, 4 or 8 kv heads) or
+    the steps on their own."""
+    n_r, n_q, k = sum(lens), 3, sum(lens) // 5
+    L = K.Layout(lens, n_q, 2 * n_kv_heads, n_kv_heads)
+    pb = K.kvc_plan_bytes(L)
+    buf = bytes_buf(pb)
+    plan = K.kvc_plan_upload(L, buf, pb)
+    rng = np.random.default_rng(n_r)
+    k_cache = rng.standard_normal((n_r, n_kv_heads, 128))
+    k_fresh = k_cache + rng.uniform(0.01, 0.2, (n_r, 1, 1)) * rng.standard_normal(k_cache.shape)
+    cache, fresh = up(oracle.f64_to_bf16(k_cache)), up(oracle.f64_to_bf16(k_fresh))
+    src = cache if in_place else up(oracle.f64_to_bf16(rng.standard_normal(k_cache.shape)))
+    before = cache.clone()
+    dev = torch.zeros(n_r, dtype=torch.float64, device="cuda:0")
+    K.kvc_kv_deviation(n_r, n_kv_heads, 128, before, fresh, dev)
+    sel = torch.full((k + n_q,), -1, dtype=torch.int32, device="cuda:0")
+    wb = K.kvc_blend_workspace(L)
+    for fill in (0, 0xFF):
+        buf.fill_(fill)
+        K.kvc_select_tokens(L, plan, (k + 0.5) / n_r, src, cache, fresh, sel, k + n_q, torch.zeros_like(bytes_buf(wb)), wb)
+        torch.cuda.synchronize()
+        assert torch.equal(cache, before)
+        got = sel.cpu().numpy()
+        assert np.array_equal(got[:k], oracle.select_topk(dev.cpu().numpy(), k))
+        assert np.array_equal(got[k:], np.arange(n_r, n_r + n_q))
