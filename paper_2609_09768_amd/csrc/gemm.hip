@@ -470,9 +470,10 @@ __device__ __forceinline__ void tile_ring(const GemmParams& P, const Lds& L, lon
       barrier_only();
     }
     if (SUB > 1 && !MAIN && B == NS - 1 && t * SUB + (kg >> 1) >= nk) {
-      // the piece lies past K
+      // the piece lies past K: both operands are zeroed, since what was loaded
+      // in its place may hold an infinity
 #pragma unroll
-      for (int i = 0; i < NT; ++i) f[set][i] = as_bf16x8(make_uint4(0, 0, 0, 0));
+      for (int i = 0; i < NF; ++i) f[set][i] = as_bf16x8(make_uint4(0, 0, 0, 0));
     }
     multiply(set, [&](int i) __attribute__((always_inline)) {
       constexpr int RPM = (NF + NM - 1) / NM;  // reads after an MFMA

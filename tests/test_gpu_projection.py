@@ -68,6 +68,25 @@ def test_projection_tiles(K, m, n, k):
     _check(_run(K, a, w, rows=rows, res=res, in_place=True), a, w, rows, res, k)
 
 
+# A row holding an infinity in its last 64 of K: no other tile size, and no
+# piece of K that only fills up a slice, may turn the infinity into a NaN.
+@pytest.mark.parametrize("m,n,k", [(150, 1032, 64), (150, 1032, 192), (63, 1032, 448), (64, 64, 704), (2047, 2056, 192),
+                                   (520, 28664, 192), (230, 37888, 576)])
+def test_projection_infinite_activation(K, m, n, k):
+    rng = np.random.default_rng(m + n + k)
+    a, w = _bf(rng, (m, k)), _bf(rng, (n, k), 0.05)
+    rows = np.arange(0, m, 7)
+    cols = k - 1 - rng.integers(0, 64, len(rows))
+    a[rows, cols] = 0x7F80                              # +inf
+    w[:, k - 64:] |= 1                                  # no zeros: inf * 0 would be a NaN of its own
+    bits = _run(K, a, w)
+    got = torch.from_numpy(bits.view(np.int16)).view(torch.bfloat16).double().numpy()
+    sign = np.sign(oracle.bf16_to_f64(w)[:, cols].T)
+    assert np.array_equal(got[rows], sign * np.inf)
+    rest = np.setdiff1d(np.arange(m), rows)
+    assert np.isfinite(got[rest]).all()
+
+
 def test_projection_small_integers_bit_exact(K):
     # products and float32 sums exact: one rounding to bf16, as the oracle
     rng = np.random.default_rng(40)
