@@ -263,11 +263,24 @@ __device__ __forceinline__ unsigned int block_scan(unsigned int v, unsigned int*
   return before + incl - v;
 }
 
-// Rank of a key of the bracket among the candidates (larger first, then lower row).
-__device__ __forceinline__ int rank_of(unsigned long long key, int row, const unsigned long long* ck, const int* cr, int n) {
+// Whether candidate c is among the first `rem` of the n candidates (larger key
+// first, then lower row), for LANES consecutive lanes that share it, each
+// comparing every LANES-th.  (Each candidate ranked by the thread that holds
+// its row, one after the other, cost up to 45 us where a hundred candidates
+// lay in few waves: 16,385 keys from the whole float64 range 57 -> 21 us,
+// 16,384 deviations 32 -> 19.)
+template <int LANES>
+__device__ __forceinline__ bool among_first(int c, long long rem, const unsigned long long* ck, const int* cr, int n) {
   int r = 0;
-  for (int j = 0; j < n; ++j) r += (ck[j] > key) || (ck[j] == key && cr[j] < row);
-  return r;
+  if (c < n) {
+    const unsigned long long key = ck[c];
+    const int row = cr[c];
+#pragma unroll 8
+    for (int j = (int)(threadIdx.x % LANES); j < n; j += LANES) r += (ck[j] > key) || (ck[j] == key && cr[j] < row);
+  }
+#pragma unroll
+  for (int m = LANES / 2; m >= 1; m >>= 1) r += __shfl_xor(r, m, 64);
+  return c < n && r < rem;
 }
 
 // One workgroup: 4,000 candidates 22 -> 9 us, 1,024 18 -> 7 us against eight
@@ -352,10 +365,14 @@ __global__ __launch_bounds__(kSmallThreads) void topk_small(const double* __rest
         cr[j] = base + i;
       }
     __syncthreads();
-    const int nc = (int)s_cand;
-#pragma unroll
-    for (int i = 0; i < ITEMS; ++i)
-      if ((in >> i & 1u) && rank_of(key[i], base + i, ck, cr, nc) < b.rem) take |= 1u << i;
+    // eight lanes a candidate; the rows taken come back through the bins,
+    // which are zero, as a mask for each thread
+    constexpr int kLanes = kSmallThreads / kMaxCand;
+    const int c = t / kLanes;
+    if (among_first<kLanes>(c, b.rem, ck, cr, (int)s_cand) && t % kLanes == 0)
+      atomicOr(&hist[cr[c] / ITEMS], 1u << (cr[c] % ITEMS));
+    __syncthreads();
+    take |= hist[t];
   } else {  // equal keys: by row
     long long rank = block_scan<kSmallWaves>((unsigned int)__popc(in), wsum, tot);
 #pragma unroll
@@ -564,12 +581,15 @@ __global__ __launch_bounds__(kThreads) void topk_fused(const double* __restrict_
   __syncthreads();
   long long sel_before = red[0];
   if (few) {
-#pragma unroll
-    for (int i = 0; i < kItems; ++i)
-      if ((in >> i & 1u) && rank_of(key[i], (int)(base + i), ck, cr, nc) < b.rem) take |= 1u << i;
-    // candidates taken in earlier workgroups
-    const bool earlier = t < nc && cr[t] < (int)(blockIdx.x * kTopkRowsPerBlock) && rank_of(ck[t], cr[t], ck, cr, nc) < b.rem;
-    sel_before += __syncthreads_count(earlier);
+    // two lanes a candidate; this workgroup's rows come back through the bins,
+    // which are zero, and those taken in earlier workgroups are counted
+    constexpr int kLanes = kThreads / kMaxCand;
+    const int c = t / kLanes;
+    const bool first = among_first<kLanes>(c, b.rem, ck, cr, nc) && t % kLanes == 0;
+    const int at = first ? cr[c] - (int)(blockIdx.x * kTopkRowsPerBlock) : 0;  // place in this workgroup's rows
+    if (first && at >= 0 && at < kTopkRowsPerBlock) atomicOr(&h[at / kItems], 1u << (at % kItems));
+    sel_before += __syncthreads_count(first && at < 0);
+    take |= h[t];
   } else if (ties) {
     const long long eq_before = red[1];
     sel_before += eq_before < b.rem ? eq_before : b.rem;

@@ -387,6 +387,20 @@ def test_select_topk_brackets(K, n):
             assert np.array_equal(_topk_gpu(K, d, k), oracle.select_topk(d, k)), k
 
 
+# The keys that are ranked one against another (at most 128) in consecutive
+# rows, so in few threads, waves or workgroups, with ties among them.
+@pytest.mark.parametrize("n", [129, 1000, 2049, 4096, 9000, 16384, 16385, 34816, 262144])
+def test_select_topk_candidates_together(K, n):
+    rng = np.random.default_rng(n)
+    for m in (2, 64, 128):
+        d = rng.random(n) * 1e-3
+        for at in (0, n // 2 - m // 2, n - m) + ((2048 - m // 2,) if n > 2048 + m else ()):
+            e = d.copy()
+            e[at:at + m] = 1.0 + rng.integers(0, m, m) * 2.0 ** -52
+            for k in (1, m // 2, m - 1, m):
+                assert np.array_equal(_topk_gpu(K, e, k), oracle.select_topk(e, k)), (m, at, k)
+
+
 # The library's own launcher with a limit on the grid barriers' waits so small
 # that they run out, at the first barrier or a later one, in some workgroups
 # or in all: the launch ends, writes nothing outside its buffers, and what it
