@@ -66,15 +66,15 @@ constexpr int kTopkRowsPerBlock = 2048;  // 256 threads x 8 rows
 inline int64_t topk_blocks(int64_t n) { return (n + kTopkRowsPerBlock - 1) / kTopkRowsPerBlock; }
 // State of the fused selection (one launch for all steps, grid barriers),
 // zero at its start: three rotating histograms, the barrier's arrival
-// counter, the range of the keys and the candidates' count.
+// counter, the candidates' count and ranges of keys (largest key, largest
+// complement): of all keys, and of those left after each histogram.
 constexpr int kTopkMaxLevels = 8;  // histograms of 256 bins that 64-bit keys can take
 struct TopkFused {
   unsigned int hist[3][256];
   unsigned int arrive;
   unsigned int cand;
-  unsigned long long max_key;
-  unsigned long long max_not;
-  unsigned int pad[58];
+  unsigned long long range[1 + kTopkMaxLevels][2];
+  unsigned int pad[26];
 };
 static_assert(sizeof(TopkFused) == 3 * 1024 + 256, "part of the workspace size");
 inline size_t topk_ws_bytes(int64_t n) {

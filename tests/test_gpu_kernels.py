@@ -401,6 +401,24 @@ def test_select_topk_candidates_together(K, n):
                 assert np.array_equal(_topk_gpu(K, e, k), oracle.select_topk(e, k)), (m, at, k)
 
 
+# Keys that a histogram cannot tell apart: equal ones, neighbours in float64
+# and clusters of both, among keys far away (several workgroups).
+@pytest.mark.parametrize("n", [16385, 34816, 262144])
+def test_select_topk_keys_close_together(K, n):
+    rng = np.random.default_rng(n + 1)
+    three = rng.integers(0, 3, n).astype(np.float64)
+    near = 1.0 + rng.permutation(n) * 2.0 ** -52
+    far = near.copy()
+    far[:3], far[3:6] = 1e300, -1e300
+    clusters = np.where(rng.random(n) < 0.5, near, 1e-200 * near)
+    mixed = np.where(rng.random(n) < 0.3, 1.0, np.where(rng.random(n) < 0.5, 1.0 + 2.0 ** -52, clusters))
+    tiny = rng.integers(0, 400, n) * 5e-324                    # subnormals and zero
+    tiny[rng.random(n) < 0.1] = -0.0
+    for d in (three, near, far, clusters, mixed, tiny):
+        for k in (1, 129, n // 7, n // 2, n - 200, n - 1):
+            assert np.array_equal(_topk_gpu(K, d, k), oracle.select_topk(d, k)), k
+
+
 # The library's own launcher with a limit on the grid barriers' waits so small
 # that they run out, at the first barrier or a later one, in some workgroups
 # or in all: the launch ends, writes nothing outside its buffers, and what it
