@@ -107,6 +107,7 @@ struct AttnParams {
   int n_kv_heads;
   int group;      // G = Hq / Hkv
   int n_subs;     // groups of 32 queries
+  int units;      // units of a workgroup, at most its waves
   int n_blocks;   // workgroups' worth of units per kv head
   float scale_log2;  // softmax scale * log2(e)
   uint16_t* out;
@@ -160,9 +161,10 @@ __global__ __launch_bounds__(kThreads) void sparse_attn_kernel(const AttnParams 
   const int block = P.n_blocks - 1 - (int)(rest / (unsigned)P.n_split);
   const long long n_kv = P.n_kv;
 
-  // this wave's unit and this lane's query (one per lane pair l, l^32)
-  const int unit = kWaves * block + wave;  // a launch has fewer than 2^23 blocks
-  const int sub = unit / P.group;
+  // this wave's unit and this lane's query (one per lane pair l, l^32); a wave
+  // past the workgroup's units has none, like the units past the last group
+  const int unit = P.units * block + wave;  // a launch has fewer than 2^23 blocks
+  const int sub = wave < P.units ? unit / P.group : P.n_subs;
   const int h = g * P.group + unit % P.group;
   const long long qi = 32ll * sub + ql;
   const bool in_range = qi < P.n_sel;
@@ -179,8 +181,8 @@ __global__ __launch_bounds__(kThreads) void sparse_attn_kernel(const AttnParams 
   // barrier before the first loads)
   int pmax = -1;
   {
-    const long long q_first = 32ll * (kWaves * block / P.group);
-    const long long q_end = std::min<long long>(32ll * ((kWaves * block + kWaves - 1) / P.group + 1), P.n_sel);
+    const long long q_first = 32ll * (P.units * block / P.group);
+    const long long q_end = std::min<long long>(32ll * ((P.units * block + P.units - 1) / P.group + 1), P.n_sel);
     for (long long q0 = q_first; q0 < q_end; q0 += 64) {
       if (q0 + lane < q_end) {
         long long pp = P.q_pos[q0 + lane];
@@ -693,6 +695,25 @@ constexpr int kMinTilesPerSplit = 4;
 
 long long div_up(long long a, long long b) { return (a + b - 1) / b; }
 
+// Units of a workgroup: eight, one a wave, but two or four where that many
+// more workgroups still run at once.  Units that reach past their smallest
+// position cost mask instructions in every tile, so eight of them in one
+// workgroup of an idle chip take longer than spread out: 40 queries of 28 / 4
+// heads over 512 keys 21.8 us with eight, 18.2 with four, 16.6 with two, 40 of
+// 9 / 1 20.1 / 16.8 / 15.7, 250 of 28 / 4 over 1,500 38.1 / 35.5 / 34.9; more
+// workgroups than CUs cost more than they give (250 of 28 / 4 in six splits
+// 23.0 with eight, in 168 workgroups, and 25.3 with four).  Only for the group
+// sizes whose units straddle query groups or fill a workgroup with one; 1, 2
+// and 4 heads a kv head keep eight (40 of 4 / 1 would gain as much, 18.6 to
+// 15.1 us, but the cut points of their split key ranges, and with them last
+// bits, would move).
+int units_per_workgroup(long long all_units, int group, int n_kv_heads, int splits) {
+  if (4 % group == 0) return kWaves;
+  for (int u = 2; u < kWaves; u *= 2)
+    if (div_up(all_units, u) * n_kv_heads * splits <= kCus) return u;
+  return kWaves;
+}
+
 // Query blocks the split and the workspace size go by: 64 queries of four
 // heads, 128 of two or 256 of one.
 long long budget_blocks(int64_t n_sel, int n_q_heads, int n_kv_heads) {
@@ -744,7 +765,6 @@ hipError_t launch_attention(const uint16_t* q, int64_t n_q_rows, const int32_t* 
   P.n_kv_heads = n_kv_heads;
   P.group = n_q_heads / n_kv_heads;
   P.n_subs = (int)div_up(n_sel, 32);
-  P.n_blocks = (int)div_up((long long)P.n_subs * P.group, kWaves);
   P.scale_log2 = scale * 1.4426950408889634f;
   P.out = out;
   P.lse = lse;
@@ -757,6 +777,8 @@ hipError_t launch_attention(const uint16_t* q, int64_t n_q_rows, const int32_t* 
     sp = (int)std::max<long long>(1, std::min<long long>(attention_splits(n_sel, n_q_heads, n_kv_heads), cap));
   }
   P.n_split = sp;
+  P.units = units_per_workgroup((long long)P.n_subs * P.group, P.group, n_kv_heads, sp);
+  P.n_blocks = (int)div_up((long long)P.n_subs * P.group, P.units);
   P.part_o = sp > 1 ? static_cast<float*>(ws) : nullptr;
   P.part_lse = sp > 1 ? P.part_o + (size_t)sp * n_sel * n_q_heads * kHeadDim : nullptr;
   hipLaunchKernelGGL(sparse_attn_kernel, dim3((unsigned)P.n_blocks * (unsigned)n_kv_heads * (unsigned)sp),

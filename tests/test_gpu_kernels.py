@@ -681,6 +681,31 @@ def test_attention_split_key_range(K, hq, hkv, n_q, n_kv):
     assert np.array_equal(got[0], np.repeat(oracle.bf16_to_f64(v[0]), hq // hkv, axis=0))
 
 
+# Heads per kv head that do not divide a workgroup's eight units (or exceed
+# them): its units come from several 32-query groups, the last of which has 1,
+# 22, 25, 31 or 32 queries, and the last workgroup has units past the end.
+@pytest.mark.parametrize("hq,hkv,n_q,n_kv", [(28, 4, 150, 3000), (28, 4, 217, 1100), (7, 1, 33, 2100), (7, 1, 1, 700),
+                                             (14, 2, 95, 1500), (20, 4, 64, 900), (6, 1, 129, 1200), (9, 1, 97, 1500),
+                                             (10, 1, 57, 600), (12, 1, 150, 2000)])
+def test_attention_groups_straddle_workgroups(K, hq, hkv, n_q, n_kv):
+    rng = np.random.default_rng(hq * 1000 + n_q)
+    pos = np.sort(rng.choice(n_kv, n_q, replace=False))
+    pos[0] = 0
+    q, k, v = _qkv(rng, n_q, n_kv, hq, hkv)
+    want, wl = oracle.sparse_query_attention(q, pos, k, v, hq, hkv)
+    assert K.kvc_attention_workspace(n_q, hq, hkv, 128) > 0
+    for split in (False, True):
+        got, lse = _attn_gpu(K, q, pos, k, v, hq, hkv, split=split)
+        ok, err = within_tol(got, want)
+        assert ok, (split, err)
+        assert np.allclose(lse, wl, rtol=0, atol=LSE_ATOL), split
+    # the order of the queries changes nothing
+    perm = rng.permutation(n_q)
+    one, lse1 = _attn_gpu(K, q, pos, k, v, hq, hkv)
+    got, lse = _attn_gpu(K, q[perm], pos[perm], k, v, hq, hkv)
+    assert np.array_equal(got, one[perm]) and np.array_equal(lse, lse1[perm])
+
+
 def test_attention_split_masks_future_keys_and_invalid_queries(K):
     rng = np.random.default_rng(16)
     n_kv, hq, hkv = 4000, 8, 2
