@@ -17,7 +17,7 @@
 //
 // One workgroup of 8 waves (two per SIMD) computes one tile of c over the
 // whole K.  The tile is 256 x 256, 256 x 192, 128 x 128 or 64 x 64, and a
-// launch mixes a large and a small one (`plan_of` below): the tiles of a
+// launch mixes a large and a small one (gemm_plan.h): the tiles of a
 // selection rarely fill 256 CUs a whole number of times, and a last round of
 // a few large tiles would cost as much as a full one.  Common to all tiles:
 // - Activation and weight rows go from memory straight into LDS in 128-byte
@@ -38,6 +38,7 @@
 //   groups of 8 row tiles, so workgroups that share activation or weight
 //   rows tend to share an L2 (1-3 % over groups of 4).
 #include "kvc_internal.h"
+#include "gemm_plan.h"
 
 #include <type_traits>
 
@@ -51,7 +52,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
 
-constexpr int kBK = 64;             // K elements of an LDS row (128 bytes)
+constexpr int kBK = kGemmSlice;     // K elements of an LDS row (128 bytes)
 constexpr int kXcds = 8;
 
 // s_waitcnt immediate (gfx9 encoding: vmcnt bits 3:0 and 15:14, expcnt 6:4,
@@ -62,7 +63,7 @@ constexpr int wait_imm(int vm, int lgkm) { return (vm & 15) | (7 << 4) | (lgkm <
 template <int I>
 using Int = std::integral_constant<int, I>;
 
-constexpr int kThreads = 512;
+constexpr int kThreads = kGemmThreads;
 constexpr int kWaves = 8;
 constexpr int kArray = 128 * kBK;   // bf16 of one LDS array: 128 rows (16 KB)
 constexpr int kGroupM = 8;          // row tiles per group of the tile walk
@@ -617,76 +618,11 @@ __global__ __launch_bounds__(kThreads) void gemm_kernel(const GemmParams P) {
   }
 }
 
-// ---- choice of tiles -----------------------------------------------------------
-// Measured time of a tile with all CUs busy, in ns: per 64 of K, and once per
-// tile (first loads, last sums and stores).  On 50 shapes of 90 to 14,000
-// rows the split these choose was within 2 % (geometric mean) of the best of
-// the splits tried.
-struct TileCost {
-  int rows, cols;
-  long long slice_ns, fixed_ns;
-  long long of(long long k) const { return slice_ns * (k / kBK) + fixed_ns; }
-};
-// large and small tiles of each mode
-constexpr TileCost kBig[3] = {{256, 256, 1400, 8000}, {256, 192, 1100, 7000}, {128, 128, 480, 1500}};
-constexpr TileCost kSmall[3] = {{128, 128, 480, 1500}, {128, 128, 480, 1500}, {64, 64, 230, 1500}};
-constexpr long long kCus = 256;
-
-long long div_up(long long a, long long b) { return (a + b - 1) / b; }
-
-// Time until all tiles are done: `big` tiles of cost cb in rounds over the
-// CUs, then `small` tiles of cost cs taken by whichever CU is free.
-long long makespan(long long big, long long cb, long long small, long long cs) {
-  const long long rounds = big / kCus, extra = big % kCus;  // extra CUs have one large tile more
-  const long long early = rounds * cb, late = early + (extra ? cb : 0);
-  if (small == 0) return late;
-  const long long free_cus = kCus - extra;
-  // the CUs that are free early take j small tiles each before the others are free
-  const long long j = extra ? cb / cs : 0;
-  if (small <= free_cus * j) return std::max(late, early + div_up(small, free_cus) * cs);
-  // after that everyone takes tiles; the early ones are at early + j cs <= late
-  const long long left = small - free_cus * j, r = left / kCus, rest = left % kCus;
-  const long long base_early = early + j * cs;
-  long long t = std::max(r > 0 ? (extra ? late : early) + r * cs : late, base_early + r * cs);
-  if (rest > 0) t = std::max(t, rest <= free_cus ? base_early + (r + 1) * cs : late + (r + 1) * cs);
-  return t;
-}
-
-struct GemmPlan {
-  int mode;
-  long long big_rows;  // row tiles of the larger size
-};
-
-// The tiles, and the split of the rows into large and small ones, with the
-// shortest estimated time.  Only the last rows are worth small tiles: as many
-// as one round of large ones covers.
-GemmPlan plan_of(long long m, long long n, long long k) {
-  GemmPlan best = {0, div_up(m, 256)};
-  long long best_t = -1;
-  for (int mode = 0; mode < 3; ++mode) {
-    const TileCost& B = kBig[mode];
-    const TileCost& S = kSmall[mode];
-    const long long all = div_up(m, B.rows), cols = div_up(n, B.cols), scols = div_up(n, S.cols);
-    const long long window = div_up(kCus, cols) + 1;
-    for (long long r = all; r >= 0 && r >= all - window; --r) {
-      const long long rest = r == all ? 0 : m - r * B.rows;
-      const long long big = r * cols, small = div_up(rest, S.rows) * scols;
-      if (big + small > (long long)UINT32_MAX / kThreads) continue;
-      const long long t = makespan(big, B.of(k), small, S.of(k));
-      if (best_t < 0 || t < best_t) {
-        best_t = t;
-        best = {mode, r};
-      }
-    }
-  }
-  return best;
-}
-
 }  // namespace
 
 int64_t gemm_work_items(int64_t m, int64_t n) {
   if (m <= 0 || n <= 0) return 0;
-  return div_up(m, 256) * div_up(n, 256) * kThreads;
+  return gemm_div_up(m, 256) * gemm_div_up(n, 256) * kThreads;
 }
 
 hipError_t launch_gemm(int64_t m, int64_t n, int64_t k, const uint16_t* a, int64_t n_a_rows,
@@ -703,15 +639,15 @@ hipError_t launch_gemm(int64_t m, int64_t n, int64_t k, const uint16_t* a, int64
   P.m = m;
   P.n = n;
   P.k = k;
-  const GemmPlan plan = plan_of(m, n, k);
-  const TileCost& B = kBig[plan.mode];
-  const TileCost& S = kSmall[plan.mode];
+  const GemmPlan plan = gemm_plan(m, n, k);
+  const GemmTile& B = kGemmBig[plan.mode];
+  const GemmTile& S = kGemmSmall[plan.mode];
   P.big_tiles_m = (int)plan.big_rows;
-  P.big_tiles_n = (int)div_up(n, B.cols);
+  P.big_tiles_n = (int)gemm_div_up(n, B.cols);
   P.big_wgs = P.big_tiles_m * P.big_tiles_n;
   P.small_row0 = plan.big_rows * B.rows;
-  P.small_tiles_m = P.small_row0 < m ? (int)div_up(m - P.small_row0, S.rows) : 0;
-  P.small_tiles_n = (int)div_up(n, S.cols);
+  P.small_tiles_m = P.small_row0 < m ? (int)gemm_div_up(m - P.small_row0, S.rows) : 0;
+  P.small_tiles_n = (int)gemm_div_up(n, S.cols);
   const unsigned wgs = (unsigned)P.big_wgs + (unsigned)P.small_tiles_m * (unsigned)P.small_tiles_n;
   if (plan.mode == 0) hipLaunchKernelGGL(gemm_kernel<0>, dim3(wgs), dim3(kThreads), 0, s, P);
   else if (plan.mode == 1) hipLaunchKernelGGL(gemm_kernel<1>, dim3(wgs), dim3(kThreads), 0, s, P);

@@ -1,0 +1,87 @@
+// Choice of the tiles of a projection launch (host code without HIP).
+//
+// A launch runs one of three pairs of tiles (modes): large ones for the first
+// rows of c and small ones for the rest (gemm.hip).
+#pragma once
+
+#include <stdint.h>
+
+#include <algorithm>
+
+namespace kvc {
+
+constexpr int kGemmSlice = 64;     // of K, per slice of a tile's loop
+constexpr int kGemmThreads = 512;  // of a workgroup: one tile
+constexpr long long kGemmCus = 256;
+
+inline long long gemm_div_up(long long a, long long b) { return (a + b - 1) / b; }
+
+// Measured time of a tile with all CUs busy, in ns: per slice, and once per
+// tile.  The latter is the first loads (about 1.5 us) and the store of the
+// tile, which every CU does at once where K is short: of 512 KB, 96 KB, 32 KB
+// or 8 KB per CU at about 3 TB/s in all, less what other workgroups' slices
+// hide where K is long.  On 139 shapes (90 to 124,000 rows, n from 64 to
+// 37,888, k from 64 to 18,944) the split these choose takes 1.3 % more than
+// the best of those tried (geometric mean; worst 21 %), and at most 4 % more
+// than 256 x 256 tiles only.  With 1,500 ns once per small tile of either size
+// it was 3.1 %, and narrow outputs of many rows and short K took small tiles
+// where large ones are better: 42,705 x 256 x 1,024 38.7 -> 32.1 us,
+// 42,705 x 256 x 4,096 131 -> 109, 30,000 x 1,024 x 64 40.2 -> 26.2.
+struct GemmTile {
+  int rows, cols;
+  long long slice_ns, once_ns;
+  constexpr long long time(long long k) const { return slice_ns * (k / kGemmSlice) + once_ns; }
+};
+// large and small tiles of each mode
+constexpr GemmTile kGemmBig[3] = {{256, 256, 1400, 8000}, {256, 192, 1100, 7000}, {128, 128, 480, 4000}};
+constexpr GemmTile kGemmSmall[3] = {{128, 128, 480, 4000}, {128, 128, 480, 4000}, {64, 64, 230, 2500}};
+
+// Time until all tiles are done: `big` tiles of cost cb in rounds over the
+// CUs, then `small` tiles of cost cs taken by whichever CU is free.
+inline long long gemm_makespan(long long big, long long cb, long long small, long long cs) {
+  const long long rounds = big / kGemmCus, extra = big % kGemmCus;  // extra CUs have one large tile more
+  const long long early = rounds * cb, late = early + (extra ? cb : 0);
+  if (small == 0) return late;
+  const long long free_cus = kGemmCus - extra;
+  // the CUs that are free early take j small tiles each before the others are free
+  const long long j = extra ? cb / cs : 0;
+  if (small <= free_cus * j) return std::max(late, early + gemm_div_up(small, free_cus) * cs);
+  // after that everyone takes tiles; the early ones are at early + j cs <= late
+  const long long left = small - free_cus * j, r = left / kGemmCus, rest = left % kGemmCus;
+  const long long base_early = early + j * cs;
+  long long t = std::max(r > 0 ? (extra ? late : early) + r * cs : late, base_early + r * cs);
+  if (rest > 0) t = std::max(t, rest <= free_cus ? base_early + (r + 1) * cs : late + (r + 1) * cs);
+  return t;
+}
+
+struct GemmPlan {
+  int mode;
+  long long big_rows;  // row tiles of the larger size
+};
+
+// The tiles, and the split of the rows into large and small ones, with the
+// shortest estimated time.  Only the last rows are worth small tiles: as many
+// as one round of large ones covers.
+inline GemmPlan gemm_plan(long long m, long long n, long long k) {
+  GemmPlan best = {0, gemm_div_up(m, 256)};
+  long long best_t = -1;
+  for (int mode = 0; mode < 3; ++mode) {
+    const GemmTile& B = kGemmBig[mode];
+    const GemmTile& S = kGemmSmall[mode];
+    const long long all = gemm_div_up(m, B.rows), cols = gemm_div_up(n, B.cols), scols = gemm_div_up(n, S.cols);
+    const long long window = gemm_div_up(kGemmCus, cols) + 1;
+    for (long long r = all; r >= 0 && r >= all - window; --r) {
+      const long long rest = r == all ? 0 : m - r * B.rows;
+      const long long big = r * cols, small = gemm_div_up(rest, S.rows) * scols;
+      if (big + small > (long long)UINT32_MAX / kGemmThreads) continue;
+      const long long t = gemm_makespan(big, B.time(k), small, S.time(k));
+      if (best_t < 0 || t < best_t) {
+        best_t = t;
+        best = {mode, r};
+      }
+    }
+  }
+  return best;
+}
+
+}  // namespace kvc
