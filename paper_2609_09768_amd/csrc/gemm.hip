@@ -622,7 +622,7 @@ __global__ __launch_bounds__(kThreads) void gemm_kernel(const GemmParams P) {
 
 int64_t gemm_work_items(int64_t m, int64_t n) {
   if (m <= 0 || n <= 0) return 0;
-  return gemm_div_up(m, 256) * gemm_div_up(n, 256) * kThreads;
+  return gemm_div_up<int64_t>(m, 256) * gemm_div_up<int64_t>(n, 256) * kThreads;
 }
 
 hipError_t launch_gemm(int64_t m, int64_t n, int64_t k, const uint16_t* a, int64_t n_a_rows,
@@ -643,11 +643,11 @@ hipError_t launch_gemm(int64_t m, int64_t n, int64_t k, const uint16_t* a, int64
   const GemmTile& B = kGemmBig[plan.mode];
   const GemmTile& S = kGemmSmall[plan.mode];
   P.big_tiles_m = (int)plan.big_rows;
-  P.big_tiles_n = (int)gemm_div_up(n, B.cols);
+  P.big_tiles_n = (int)gemm_div_up<int64_t>(n, B.cols);
   P.big_wgs = P.big_tiles_m * P.big_tiles_n;
   P.small_row0 = plan.big_rows * B.rows;
-  P.small_tiles_m = P.small_row0 < m ? (int)gemm_div_up(m - P.small_row0, S.rows) : 0;
-  P.small_tiles_n = (int)gemm_div_up(n, S.cols);
+  P.small_tiles_m = P.small_row0 < m ? (int)gemm_div_up<int64_t>(m - P.small_row0, S.rows) : 0;
+  P.small_tiles_n = (int)gemm_div_up<int64_t>(n, S.cols);
   const unsigned wgs = (unsigned)P.big_wgs + (unsigned)P.small_tiles_m * (unsigned)P.small_tiles_n;
   if (plan.mode == 0) hipLaunchKernelGGL(gemm_kernel<0>, dim3(wgs), dim3(kThreads), 0, s, P);
   else if (plan.mode == 1) hipLaunchKernelGGL(gemm_kernel<1>, dim3(wgs), dim3(kThreads), 0, s, P);

@@ -14,7 +14,8 @@ constexpr int kGemmSlice = 64;     // of K, per slice of a tile's loop
 constexpr int kGemmThreads = 512;  // of a workgroup: one tile
 constexpr long long kGemmCus = 256;
 
-inline long long gemm_div_up(long long a, long long b) { return (a + b - 1) / b; }
+template <typename T>
+constexpr T gemm_div_up(T a, T b) { return (a + b - 1) / b; }
 
 // Measured time of a tile with all CUs busy, in ns: per slice, and once per
 // tile.  The latter is the first loads (about 1.5 us) and the store of the
@@ -37,15 +38,17 @@ constexpr GemmTile kGemmBig[3] = {{256, 256, 1400, 8000}, {256, 192, 1100, 7000}
 constexpr GemmTile kGemmSmall[3] = {{128, 128, 480, 4000}, {128, 128, 480, 4000}, {64, 64, 230, 2500}};
 
 // Time until all tiles are done: `big` tiles of cost cb in rounds over the
-// CUs, then `small` tiles of cost cs taken by whichever CU is free.
-inline long long gemm_makespan(long long big, long long cb, long long small, long long cs) {
+// CUs, then `small` tiles of cost cs taken by whichever CU is free; cb_cs =
+// cb / cs.  (A narrow output of many rows has some 770 splits to try, and a
+// division of 64-bit numbers costs ten times the rest of a step.)
+inline long long gemm_makespan(long long big, long long cb, long long small, long long cs, long long cb_cs) {
   const long long rounds = big / kGemmCus, extra = big % kGemmCus;  // extra CUs have one large tile more
   const long long early = rounds * cb, late = early + (extra ? cb : 0);
   if (small == 0) return late;
   const long long free_cus = kGemmCus - extra;
   // the CUs that are free early take j small tiles each before the others are free
-  const long long j = extra ? cb / cs : 0;
-  if (small <= free_cus * j) return std::max(late, early + gemm_div_up(small, free_cus) * cs);
+  const long long j = extra ? cb_cs : 0;
+  if (small <= free_cus * j) return std::max(late, early + (long long)gemm_div_up((uint32_t)small, (uint32_t)free_cus) * cs);
   // after that everyone takes tiles; the early ones are at early + j cs <= late
   const long long left = small - free_cus * j, r = left / kGemmCus, rest = left % kGemmCus;
   const long long base_early = early + j * cs;
@@ -59,28 +62,37 @@ struct GemmPlan {
   long long big_rows;  // row tiles of the larger size
 };
 
-// The tiles, and the split of the rows into large and small ones, with the
-// shortest estimated time.  Only the last rows are worth small tiles: as many
-// as one round of large ones covers.
-inline GemmPlan gemm_plan(long long m, long long n, long long k) {
-  GemmPlan best = {0, gemm_div_up(m, 256)};
-  long long best_t = -1;
-  for (int mode = 0; mode < 3; ++mode) {
-    const GemmTile& B = kGemmBig[mode];
-    const GemmTile& S = kGemmSmall[mode];
-    const long long all = gemm_div_up(m, B.rows), cols = gemm_div_up(n, B.cols), scols = gemm_div_up(n, S.cols);
-    const long long window = gemm_div_up(kGemmCus, cols) + 1;
-    for (long long r = all; r >= 0 && r >= all - window; --r) {
-      const long long rest = r == all ? 0 : m - r * B.rows;
-      const long long big = r * cols, small = gemm_div_up(rest, S.rows) * scols;
-      if (big + small > (long long)UINT32_MAX / kGemmThreads) continue;
-      const long long t = gemm_makespan(big, B.time(k), small, S.time(k));
-      if (best_t < 0 || t < best_t) {
-        best_t = t;
-        best = {mode, r};
-      }
+// The best split of one mode's tiles, if it takes less than best_t.
+template <int MODE>
+inline void gemm_best_split(long long m, long long n, long long k, GemmPlan& best, long long& best_t) {
+  constexpr GemmTile B = kGemmBig[MODE], S = kGemmSmall[MODE];
+  const long long all = gemm_div_up<long long>(m, B.rows), cols = gemm_div_up<long long>(n, B.cols);
+  const long long scols = gemm_div_up<long long>(n, S.cols);
+  const long long cb = B.time(k), cs = S.time(k), cb_cs = cb / cs;
+  const long long window = gemm_div_up(kGemmCus, cols) + 1;
+  for (long long r = all; r >= 0 && r >= all - window; --r) {
+    const long long rest = r == all ? 0 : m - r * B.rows;
+    const long long big = r * cols, small = gemm_div_up<long long>(rest, S.rows) * scols;
+    if (big + small > (long long)UINT32_MAX / kGemmThreads) continue;
+    const long long t = gemm_makespan(big, cb, small, cs, cb_cs);
+    if (best_t < 0 || t < best_t) {
+      best_t = t;
+      best = {MODE, r};
     }
   }
+}
+
+// The tiles, and the split of the rows into large and small ones, with the
+// shortest estimated time.  Only the last rows are worth small tiles: as many
+// as one round of large ones covers.  It takes the host up to 4 us for outputs
+// of at most 256 columns (5.5, 8 to 10 on another CPU, with the tiles' sizes
+// as variables and every division in 64 bits), below 0.7 from 1,024 columns on.
+inline GemmPlan gemm_plan(long long m, long long n, long long k) {
+  GemmPlan best = {0, gemm_div_up(m, 256ll)};
+  long long best_t = -1;
+  gemm_best_split<0>(m, n, k, best, best_t);
+  gemm_best_split<1>(m, n, k, best, best_t);
+  gemm_best_split<2>(m, n, k, best, best_t);
   return best;
 }
 
