@@ -345,3 +345,32 @@ def test_select_tokens_overwritten_plan(K, n_kv_heads, lens, in_place):
         got = sel.cpu().numpy()
         assert np.array_equal(got[:k], oracle.select_topk(dev.cpu().numpy(), k))
         assert np.array_equal(got[k:], np.arange(n_r, n_r + n_q))
+
+
+@pytest.mark.parametrize("n_kv_heads", [1, 2, 3, 4, 8])
+def test_select_tokens_workspace_in_use(K, n_kv_heads):
+    """Above 16,384 candidates the deviation's launch clears the selection's
+    state (one variant of it for each of 1, 2, 4 and 8 kv heads, one for other
+    counts): a workspace that holds anything, or an earlier selection, gives
+    the same selection."""
+    lens, n_q, k = (9000, 7400), 5, 2500
+    n_r = sum(lens)
+    L = K.Layout(lens, n_q, n_kv_heads, n_kv_heads)
+    pb, wb = K.kvc_plan_bytes(L), K.kvc_blend_workspace(L)
+    plan = K.kvc_plan_upload(L, bytes_buf(pb), pb)
+    ws = torch.full((wb,), 0x01, dtype=torch.uint8, device="cuda:0")   # every count 0x01010101
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(n_kv_heads)
+    shape = (n_r, n_kv_heads, 128)
+    for _ in range(3):
+        src = torch.randn(shape, generator=g, device="cuda:0").to(torch.bfloat16).view(torch.int16)
+        fresh = torch.randn(shape, generator=g, device="cuda:0").to(torch.bfloat16).view(torch.int16)
+        cache = torch.zeros_like(src)
+        sel = torch.full((k + n_q,), -1, dtype=torch.int32, device="cuda:0")
+        K.kvc_select_tokens(L, plan, (k + 0.5) / n_r, src, cache, fresh, sel, k + n_q, ws, wb)
+        dev = torch.zeros(n_r, dtype=torch.float64, device="cuda:0")
+        K.kvc_kv_deviation(n_r, n_kv_heads, 128, cache, fresh, dev)
+        torch.cuda.synchronize()
+        got = sel.cpu().numpy()
+        assert np.array_equal(got[:k], oracle.select_topk(dev.cpu().numpy(), k))
+        assert np.array_equal(got[k:], np.arange(n_r, n_r + n_q))

@@ -681,12 +681,13 @@ def test_attention_split_key_range(K, hq, hkv, n_q, n_kv):
     assert np.array_equal(got[0], np.repeat(oracle.bf16_to_f64(v[0]), hq // hkv, axis=0))
 
 
-# Heads per kv head that do not divide a workgroup's eight units (or exceed
-# them): its units come from several 32-query groups, the last of which has 1,
-# 22, 25, 31 or 32 queries, and the last workgroup has units past the end.
-@pytest.mark.parametrize("hq,hkv,n_q,n_kv", [(28, 4, 150, 3000), (28, 4, 217, 1100), (7, 1, 33, 2100), (7, 1, 1, 700),
+# Heads per kv head that do not divide a workgroup's units (or exceed them):
+# two, four and (the last two shapes) eight units that come from several
+# 32-query groups, incomplete last groups, and units past the end in the last
+# workgroup.
+@pytest.mark.parametrize("hq,hkv,n_q,n_kv", [(28, 4, 150, 3000), (28, 4, 217, 1100), (7, 1, 33, 2100), (12, 4, 70, 800),
                                              (14, 2, 95, 1500), (20, 4, 64, 900), (6, 1, 129, 1200), (9, 1, 97, 1500),
-                                             (10, 1, 57, 600), (12, 1, 150, 2000)])
+                                             (10, 1, 57, 600), (12, 1, 150, 2000), (28, 4, 1190, 1300), (40, 8, 700, 900)])
 def test_attention_groups_straddle_workgroups(K, hq, hkv, n_q, n_kv):
     rng = np.random.default_rng(hq * 1000 + n_q)
     pos = np.sort(rng.choice(n_kv, n_q, replace=False))

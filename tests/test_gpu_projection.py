@@ -52,13 +52,15 @@ def test_projection_shapes(K, m, n, k):
 
 # Tile sizes and the lengths of their K pipelines: 64-wide tiles with 1 to 6
 # slices of 128 (the last one half empty for odd k / 64), 128-wide tiles with
-# 1 to 7 slices of 64, 256-row tiles of 256 columns with 2 to 6 and of 192 with
-# 8 and 9, and launches that mix two sizes (rows past the last full large tile).
+# 1 to 7 slices of 64, 256-row tiles of 256 columns with 1 to 6 and of 192 with
+# 5, 6, 8 and 9, and launches that mix two sizes (rows past the last full large
+# tile).
 @pytest.mark.parametrize("m,n,k", [(150, 1032, 64), (150, 1032, 128), (65, 72, 192), (150, 1032, 320), (63, 1032, 448),
                                    (150, 1032, 576), (64, 64, 704), (2050, 2056, 64), (2050, 2056, 128),
                                    (2047, 2056, 192), (2050, 2056, 320), (2050, 2056, 448), (700, 6144, 256),
-                                   (520, 28664, 128), (520, 28664, 192), (500, 28664, 256), (520, 24560, 320),
-                                   (520, 24560, 384), (230, 37888, 512), (230, 37888, 576), (500, 37888, 512)])
+                                   (520, 28664, 64), (520, 28664, 128), (520, 28664, 192), (500, 28664, 256),
+                                   (520, 28664, 320), (500, 28664, 384), (520, 24560, 320), (520, 24560, 384),
+                                   (230, 37888, 512), (230, 37888, 576), (500, 37888, 512)])
 def test_projection_tiles(K, m, n, k):
     rng = np.random.default_rng(m + 3 * n + k)
     a, w = _bf(rng, (m + 3, k)), _bf(rng, (n, k), 0.05)
