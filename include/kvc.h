@@ -406,7 +406,7 @@ kvc_status kvc_projection(int64_t m, int64_t n, int64_t k, const void* a, int64_
  *      whose source directly follows the previous chunk's in memory is
  *      copied with it, so a caller holding the chunks back to back pays one
  *      copy per tensor; 16-byte aligned copies below 1 MB from pinned host
- *      memory, and those inside the GPU's memory, share kernel launches
+ *      memory, and below 16 MB inside the GPU's memory, share kernel launches
  *      (which read host memory in place) instead of one transfer each;
  *   2. one kernel that writes zeros (+0.0) into the K and V rows of the
  *      zero_kv chunks and adjusts the keys of every other chunk in place,

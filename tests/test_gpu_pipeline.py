@@ -277,3 +277,28 @@ def test_stage_layer_pinned_source_rewritten(K):
         fill()
         g.replay()
         check()
+
+
+@pytest.mark.parametrize("host", [False, True])
+def test_stage_layer_copies_about_the_size_left_to_the_runtime(K, host):
+    """Runs just below, at and just above the sizes from which a copy leaves
+    the list (16 MB in device memory, 1 MB in pinned host memory), with small
+    fragments between them."""
+    edge = ((1 << 20) if host else (16 << 20)) // (8 * 256)
+    lens = (edge - 1, 3, edge, 1, edge + 1, 40)
+    w = W.Workload("edges", lens, 0, 8, 8)
+    L, plan = _layout_plan(K, w, zero=False)
+    n_r, row0 = w.n_reused, np.concatenate([[0], np.cumsum(lens)])
+    g = torch.Generator().manual_seed(edge)
+    src = torch.randint(0, 2 ** 14, (2, n_r, 8, 128), generator=g, dtype=torch.int16)
+    arena = torch.zeros((2, n_r + len(lens), 8, 128), dtype=torch.int16)     # a row between fragments
+    for i, n in enumerate(lens):
+        arena[:, row0[i] + i:row0[i] + i + n] = src[:, row0[i]:row0[i + 1]]
+    arena = arena.pin_memory() if host else arena.cuda()
+    ptrs = [[arena[t, row0[i] + i].data_ptr() for i in range(len(lens))] for t in range(2)]
+    kc, vc, want_k = (torch.zeros((n_r, 8, 128), dtype=torch.int16, device="cuda:0") for _ in range(3))
+    K.kvc_stage_layer(L, plan, ptrs[0], ptrs[1], kc, vc)
+    K.kvc_rope_shift(L, plan, src[0].cuda(), want_k)
+    torch.cuda.synchronize()
+    assert torch.equal(kc, want_k)
+    assert torch.equal(vc.cpu(), src[1])
