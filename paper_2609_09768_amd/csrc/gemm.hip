@@ -28,8 +28,8 @@
 //   consecutive rows, one piece) fall in 16 distinct bank groups.
 // - The MFMA computes each 16 x 16 block transposed (weight rows as the
 //   first operand), so a lane ends with one output row and four consecutive
-//   columns per block: 8-byte stores, and 8-byte residual loads, issued
-//   together before the first store.
+//   columns per block: 8-byte stores (16 for the large tiles, see store_wave)
+//   and residual loads, issued together before the first store.
 // - LDS is eight arrays of 16 KB, four for each operand, so that the
 //   compiler's wait-count pass can tell loads in flight into one from the
 //   reads of another; every wait for a load is explicit.
@@ -179,29 +179,109 @@ __device__ __forceinline__ uint2 residual4(const GemmParams& P, long long m, lon
   return *reinterpret_cast<const uint2*>(P.res + min(m, P.m - 1) * P.n + min(n, P.n - 4));
 }
 
+__device__ __forceinline__ f32x4 residual_f32(const uint2& r2) {
+  return f32x4{__uint_as_float(r2.x << 16), __uint_as_float(r2.x & 0xFFFF0000u), __uint_as_float(r2.y << 16),
+               __uint_as_float(r2.y & 0xFFFF0000u)};
+}
+
 // Four consecutive outputs of row m from column n.
 __device__ __forceinline__ void store4(const GemmParams& P, long long m, long long n, bool zero, const f32x4& acc,
                                        const uint2& r2) {
   if (m >= P.m || n >= P.n) return;
-  float v[4];
-#pragma unroll
-  for (int e = 0; e < 4; ++e) v[e] = zero ? 0.f : acc[e];
-  if (P.res) {
-    v[0] += __uint_as_float(r2.x << 16);
-    v[1] += __uint_as_float(r2.x & 0xFFFF0000u);
-    v[2] += __uint_as_float(r2.y << 16);
-    v[3] += __uint_as_float(r2.y & 0xFFFF0000u);
-  }
+  f32x4 v = zero ? f32x4{0.f, 0.f, 0.f, 0.f} : acc;
+  if (P.res) v += residual_f32(r2);
   *reinterpret_cast<uint2*>(P.c + m * P.n + n) = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
+}
+
+// Two adjacent 16-column blocks of 16 output rows, four columns of each in a
+// lane, to 16 bytes of one block in a lane and back: lanes of even q = lane / 16
+// get columns 4 q .. 4 q + 7 of the first block, those of odd q columns
+// 4 (q - 1) .. of the second.
+__device__ __forceinline__ void swap_blocks(uint2& a, uint2& b) {
+  const auto x = __builtin_amdgcn_permlane16_swap(a.x, b.x, false, false);
+  const auto y = __builtin_amdgcn_permlane16_swap(a.y, b.y, false, false);
+  a = make_uint2(x[0], y[0]);
+  b = make_uint2(x[1], y[1]);
+}
+
+// The outputs of a wave of tile_256: 16 rows each at m and m + 128, + 16, + 32
+// and + 48, 16 NT columns from n on.  ZERO: some row is a gather of an invalid
+// entry.  Two blocks are stored together, 64 bytes of a row in one instruction,
+// and an address is a scalar per 16 rows, the lane's offset from it and a
+// constant.  The L2 takes about one piece of a line per store instruction and
+// row, and every CU stores its tile at once, so stores of 32 bytes of a row (8
+// a lane, 37 instructions each) cost more than the K loop where K is short:
+// 8,192 x 8,192 x 64 46.2 -> 36.9 us, x 512 94 -> 85, 30,000 x 4,096 x 64 86 ->
+// 62, 18,856 x 28,672 x 4,096 3,280 -> 3,185.  (Non-temporal stores, which the
+// L2 does not gather into lines, took four times as long.)
+template <int NT, bool RES, bool ZERO>
+__device__ __forceinline__ void store_wave(const GemmParams& P, long long m, long long n, int lane,
+                                           const f32x4 (&acc)[NT][2][4]) {
+  const int rl = lane & 15, q = lane >> 4;
+  // first column of this lane's piece of a pair of blocks (n is a multiple of
+  // 8, so it lies in c as a whole or not at all), and of a single block
+  const int pair_col = 16 * (q & 1) + 4 * (q & 2), one_col = 4 * q;
+  // bytes, below 2^30
+  const uint32_t pair_off = (uint32_t)(rl * (int)P.n + pair_col) * 2, one_off = (uint32_t)(rl * (int)P.n + one_col) * 2;
+  bool in[NT];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) in[nt] = n + 16 * nt + (nt + 1 < NT || !(NT & 1) ? pair_col : one_col) < P.n;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const long long mh = m + 128 * h;
+    uint2 r[4][NT];
+    if (RES) {
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt) {
+        const bool row = mh + 16 * mt + rl < P.m;
+        const char* src = reinterpret_cast<const char*>(P.res + (mh + 16 * mt) * P.n + n);
+#pragma unroll
+        for (int nt = 0; nt + 1 < NT; nt += 2) {
+          uint4 u = make_uint4(0, 0, 0, 0);
+          if (row && in[nt]) u = *reinterpret_cast<const uint4*>(src + pair_off + 32 * nt);
+          r[mt][nt] = make_uint2(u.x, u.y);
+          r[mt][nt + 1] = make_uint2(u.z, u.w);
+        }
+        if (NT & 1) {
+          r[mt][NT - 1] = make_uint2(0, 0);
+          if (row && in[NT - 1]) r[mt][NT - 1] = *reinterpret_cast<const uint2*>(src + one_off + 32 * (NT - 1));
+        }
+      }
+    }
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) {
+      const bool row = mh + 16 * mt + rl < P.m;
+      const bool zero = ZERO && zero_row(P, mh + 16 * mt + rl);
+      char* dst = reinterpret_cast<char*>(P.c + (mh + 16 * mt) * P.n + n);
+      uint2 o[NT];
+      if (RES) {
+#pragma unroll
+        for (int nt = 0; nt + 1 < NT; nt += 2) swap_blocks(r[mt][nt], r[mt][nt + 1]);
+      }
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        f32x4 v = zero ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[nt][h][mt];
+        if (RES) v += residual_f32(r[mt][nt]);
+        o[nt] = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
+      }
+#pragma unroll
+      for (int nt = 0; nt + 1 < NT; nt += 2) {
+        swap_blocks(o[nt], o[nt + 1]);
+        if (row && in[nt])
+          *reinterpret_cast<uint4*>(dst + pair_off + 32 * nt) = make_uint4(o[nt].x, o[nt].y, o[nt + 1].x, o[nt + 1].y);
+      }
+      if ((NT & 1) && row && in[NT - 1]) *reinterpret_cast<uint2*>(dst + one_off + 32 * (NT - 1)) = o[NT - 1];
+    }
+  }
 }
 
 // A tile of 256 rows and 64 NT columns (NT = 4 or 3) in K slices of 64, two of
 // them in LDS.  Each wave owns 64 rows of each half of the tile's rows and NT
-// blocks of 16 columns, adjacent ones where it can, for the stores.  A slice is
-// two phases (figures for NT = 4): the tile's upper rows (16 fragments read,
-// 32 MFMAs), then the lower ones (8 read, 32 MFMAs).  The two waves of a SIMD run half a phase apart (waves
-// 4..7 pass one barrier more at the start): while one reads its fragments
-// and issues the loads, the other keeps the matrix cores busy.  A half tile
+// adjacent blocks of 16 columns.  A slice is two phases (figures for NT = 4):
+// the tile's upper rows (16 fragments read, 32 MFMAs), then the lower ones (8
+// read, 32 MFMAs).  The two waves of a SIMD run half a phase apart (waves 4..7
+// pass one barrier more at the start): while one reads its fragments and
+// issues the loads, the other keeps the matrix cores busy.  A half tile
 // is refilled as soon as both have read it, one phase later, so a load has
 // a whole slice (about 0.9 us) to arrive.  Alone on the chip a tile takes
 // 0.93 us per slice (2 x 1031 MFMA cycles are 0.86 us at 2.4 GHz); with all
@@ -225,9 +305,14 @@ __device__ __forceinline__ void tile_256(const GemmParams& P, const Lds& S, int 
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const long long m0 = (long long)tm * 256, n0 = (long long)tn * (64 * NT);
   const int wn = wave & 3;
-  // this wave's 16-column block nt begins at column 128 (nt / 2) + strip(nt):
-  // two adjacent blocks of each 128 columns, one of a last 64
+  // The LDS rows of this wave's block nt begin at 128 (nt / 2) + strip(nt), and
+  // LDS row `row` holds weight row column(row) of the tile: each wave's blocks
+  // lie in both of the operand's arrays, and are adjacent columns of c.
   auto strip = [&](int nt) __attribute__((always_inline)) { return nt < 2 || NT == 4 ? 32 * wn + 16 * (nt & 1) : 16 * wn; };
+  auto column = [&](int row) __attribute__((always_inline)) {
+    return row < 128 ? 16 * NT * (row >> 5) + (row & 31)
+                     : NT == 4 ? 64 * ((row - 128) >> 5) + 32 + (row & 31) : 48 * ((row - 128) >> 4) + 32 + (row & 15);
+  };
   const int wm = wave >> 2;  // rows 64 wm .. +63 of each half
 
   const uint16_t* a_src[2][2];
@@ -242,7 +327,7 @@ __device__ __forceinline__ void tile_256(const GemmParams& P, const Lds& S, int 
 #pragma unroll
   for (int j = 0; j < NT; ++j) {
     const int row = 64 * j + 8 * wave + (lane >> 3);
-    w_src[j] = w_source(P, n0 + row) + 8 * ((lane & 7) ^ ((row >> 1) & 7));
+    w_src[j] = w_source(P, n0 + column(row)) + 8 * ((lane & 7) ^ ((row >> 1) & 7));
   }
   auto load_half = [&](const uint16_t* const (&src)[2], int t, uint16_t* dst) __attribute__((always_inline)) {
 #pragma unroll
@@ -353,23 +438,20 @@ __device__ __forceinline__ void tile_256(const GemmParams& P, const Lds& S, int 
   }
   if (wm == 0) barrier_only();
 
+  bool zero = false;
+  if (P.a_rows) {
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const long long m = m0 + 128 * h + 64 * wm + rl;
-    const long long n = n0 + 4 * q;
-    uint2 r[4][NT];
-    bool zero[4];
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-      zero[mt] = zero_row(P, m + 16 * mt);
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) r[mt][nt] = residual4(P, m + 16 * mt, n + 128 * (nt >> 1) + strip(nt));
-    }
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
-        store4(P, m + 16 * mt, n + 128 * (nt >> 1) + strip(nt), zero[mt], acc[nt][h][mt], r[mt][nt]);
+      for (int mt = 0; mt < 4; ++mt) zero |= zero_row(P, m0 + 128 * h + 64 * wm + 16 * mt + rl);
+  }
+  const long long mw = m0 + 64 * wm, nw = n0 + 16 * NT * wn;
+  if (__any(zero)) {
+    if (P.res) store_wave<NT, true, true>(P, mw, nw, lane, acc);
+    else store_wave<NT, false, true>(P, mw, nw, lane, acc);
+  } else {
+    if (P.res) store_wave<NT, true, false>(P, mw, nw, lane, acc);
+    else store_wave<NT, false, false>(P, mw, nw, lane, acc);
   }
 }
 

@@ -70,6 +70,23 @@ def test_projection_tiles(K, m, n, k):
     _check(_run(K, a, w, rows=rows, res=res, in_place=True), a, w, rows, res, k)
 
 
+# Wide stores of large tiles that lie inside c (256 and 192 columns), beside
+# tiles at the edges: no residual, and one kept apart from c; no gather, and
+# one whose only invalid entry leaves most waves of its tile on that path.
+@pytest.mark.parametrize("m,n,k", [(520, 28664, 128), (500, 37888, 512)])
+def test_projection_tiles_inside(K, m, n, k):
+    rng = np.random.default_rng(m + n)
+    a, w = _bf(rng, (m, k)), _bf(rng, (n, k), 0.05)
+    res = _bf(rng, (m, n))
+    _check(_run(K, a, w), a, w, None, None, k)
+    _check(_run(K, a, w, res=res), a, w, None, res, k)
+    rows = rng.permutation(m)
+    rows[70] = m
+    got = _run(K, a, w, rows=rows)
+    _check(got, a, w, rows, None, k)
+    assert not got[70].any()
+
+
 # A row holding an infinity in its last 64 of K: no other tile size, and no
 # piece of K that only fills up a slice, may turn the infinity into a NaN.
 @pytest.mark.parametrize("m,n,k", [(150, 1032, 64), (150, 1032, 192), (63, 1032, 448), (64, 64, 704), (2047, 2056, 192),
