@@ -36,7 +36,12 @@
 // - Workgroup ids are dispatched round-robin over the 8 XCDs; they are
 //   renumbered so that each XCD gets a contiguous range of tiles, walked in
 //   groups of 8 row tiles, so workgroups that share activation or weight
-//   rows tend to share an L2 (1-3 % over groups of 4).
+//   rows tend to share an L2 (5,056 x 28,672 x 4,096 836 us, 864 with groups of
+//   4).  Where K is short, an XCD's tiles that are stored together matter more
+//   than those rows, and groups of 4 make them twice as wide: 17,339 x 29,064 x
+//   320 472 us instead of 560, x 1,024 902 and 987, 14,227 x 17,720 x 128 158
+//   and 171, 18,856 x 28,672 x 1,024 969 and 968; up to 6 % slower for a few
+//   (40,000 x 8,192 x 320 313 and 294), and groups of 16 are worse.
 #include "kvc_internal.h"
 #include "gemm_plan.h"
 
@@ -66,7 +71,6 @@ using Int = std::integral_constant<int, I>;
 constexpr int kThreads = kGemmThreads;
 constexpr int kWaves = 8;
 constexpr int kArray = 128 * kBK;   // bf16 of one LDS array: 128 rows (16 KB)
-constexpr int kGroupM = 8;          // row tiles per group of the tile walk
 
 struct GemmParams {
   const uint16_t* a;
@@ -81,6 +85,7 @@ struct GemmParams {
   int big_wgs, big_tiles_m, big_tiles_n;
   int small_tiles_m, small_tiles_n;
   long long small_row0;
+  int group_m;  // row tiles per group of the tile walk
 };
 
 // The eight LDS arrays of a workgroup.
@@ -107,17 +112,17 @@ __device__ __forceinline__ void barrier_only() {
 
 // Workgroup id -> (row tile, column tile).  Ids go round-robin over the
 // XCDs; v renumbers them so each XCD holds a contiguous range of v (a
-// bijection on [0, T)), and v walks groups of kGroupM row tiles column by
+// bijection on [0, T)), and v walks groups of group_m row tiles column by
 // column.
-__device__ __forceinline__ void tile_of(int bid, int tiles_m, int tiles_n, int& tm, int& tn) {
+__device__ __forceinline__ void tile_of(int bid, int tiles_m, int tiles_n, int group_m, int& tm, int& tn) {
   const int total = tiles_m * tiles_n;
   const int per = total / kXcds, rem = total % kXcds;
   const int x = bid % kXcds, slot = bid / kXcds;
   const int v = x * per + min(x, rem) + slot;
-  const int group = v / (kGroupM * tiles_n);
-  const int first = group * kGroupM;
-  const int gm = min(kGroupM, tiles_m - first);
-  const int in_group = v - group * kGroupM * tiles_n;
+  const int group = v / (group_m * tiles_n);
+  const int first = group * group_m;
+  const int gm = min(group_m, tiles_m - first);
+  const int in_group = v - group * group_m * tiles_n;
   tm = first + in_group % gm;
   tn = in_group / gm;
 }
@@ -689,12 +694,12 @@ __global__ __launch_bounds__(kThreads) void gemm_kernel(const GemmParams P) {
   const Lds S = {A0, A1, A2, A3, W0, W1, W2, W3};
   int tm, tn;
   if ((int)blockIdx.x < P.big_wgs) {
-    tile_of((int)blockIdx.x, P.big_tiles_m, P.big_tiles_n, tm, tn);
+    tile_of((int)blockIdx.x, P.big_tiles_m, P.big_tiles_n, P.group_m, tm, tn);
     if constexpr (MODE == 0) tile_256<4>(P, S, tm, tn);
     else if constexpr (MODE == 1) tile_256<3>(P, S, tm, tn);
     else tile_ring<128, 2, 2, 2>(P, S, (long long)tm * 128, tn);
   } else {
-    tile_of((int)blockIdx.x - P.big_wgs, P.small_tiles_m, P.small_tiles_n, tm, tn);
+    tile_of((int)blockIdx.x - P.big_wgs, P.small_tiles_m, P.small_tiles_n, P.group_m, tm, tn);
     if constexpr (MODE < 2) tile_ring<128, 2, 2, 2>(P, S, P.small_row0 + (long long)tm * 128, tn);
     else tile_ring<64, 2, 1, 4>(P, S, P.small_row0 + (long long)tm * 64, tn);
   }
@@ -730,6 +735,7 @@ hipError_t launch_gemm(int64_t m, int64_t n, int64_t k, const uint16_t* a, int64
   P.small_row0 = plan.big_rows * B.rows;
   P.small_tiles_m = P.small_row0 < m ? (int)gemm_div_up<int64_t>(m - P.small_row0, S.rows) : 0;
   P.small_tiles_n = (int)gemm_div_up<int64_t>(n, S.cols);
+  P.group_m = k < 2048 ? 4 : 8;
   const unsigned wgs = (unsigned)P.big_wgs + (unsigned)P.small_tiles_m * (unsigned)P.small_tiles_n;
   if (plan.mode == 0) hipLaunchKernelGGL(gemm_kernel<0>, dim3(wgs), dim3(kThreads), 0, s, P);
   else if (plan.mode == 1) hipLaunchKernelGGL(gemm_kernel<1>, dim3(wgs), dim3(kThreads), 0, s, P);
