@@ -19,22 +19,26 @@ constexpr T gemm_div_up(T a, T b) { return (a + b - 1) / b; }
 
 // Measured time of a tile with all CUs busy, in ns: per slice, and once per
 // tile.  The latter is the first loads (about 1.5 us) and the store of the
-// tile, which every CU does at once where K is short: of 512 KB, 96 KB, 32 KB
-// or 8 KB per CU at about 3 TB/s in all, less what other workgroups' slices
-// hide where K is long.  On 139 shapes (90 to 124,000 rows, n from 64 to
-// 37,888, k from 64 to 18,944) the split these choose takes 1.3 % more than
-// the best of those tried (geometric mean; worst 21 %), and at most 4 % more
-// than 256 x 256 tiles only.  With 1,500 ns once per small tile of either size
-// it was 3.1 %, and narrow outputs of many rows and short K took small tiles
-// where large ones are better: 42,705 x 256 x 1,024 38.7 -> 32.1 us,
-// 42,705 x 256 x 4,096 131 -> 109, 30,000 x 1,024 x 64 40.2 -> 26.2.
+// tile, which every CU does at once where K is short (128 KB, 96 KB, 32 KB or
+// 8 KB per CU), less what other workgroups' slices hide where K is long: the
+// large tile's is 6.9 us at 4,096 x 16,384 x 128, 7.5 at 8,192 x 8,192 x 1,024
+// and 3.9 at 16,200 x 1,024 x 4,096.  The large tiles' values are those that
+// choose best: with 8,000 and 7,000, right for stores of 32 bytes a row, 106
+// shapes of short K on which the choice differs took 4.5 % more (754 x 25,640 x
+// 576 37 -> 29 us, 1,281 x 4,096 x 512 16.6 -> 14.8), with 5,000 and 4,500 0.5 %.
+// Of the 1,500 ns that small tiles once had: narrow outputs of many rows and
+// short K took small tiles where large ones are better (42,705 x 256 x 1,024
+// 38.7 -> 32.1 us, 42,705 x 256 x 4,096 131 -> 109).  On 440 random shapes (1
+// to 23,000 rows, n from 64 to 37,000, k from 64 to 18,800) the launch takes
+// 0.43 of the time of 256 x 256 tiles alone with one barrier per slice
+// (geometric mean), and at most 3 % more (7,619 x 7,432 x 256).
 struct GemmTile {
   int rows, cols;
   long long slice_ns, once_ns;
   constexpr long long time(long long k) const { return slice_ns * (k / kGemmSlice) + once_ns; }
 };
 // large and small tiles of each mode
-constexpr GemmTile kGemmBig[3] = {{256, 256, 1400, 8000}, {256, 192, 1100, 7000}, {128, 128, 480, 4000}};
+constexpr GemmTile kGemmBig[3] = {{256, 256, 1400, 6000}, {256, 192, 1100, 5500}, {128, 128, 480, 4000}};
 constexpr GemmTile kGemmSmall[3] = {{128, 128, 480, 4000}, {128, 128, 480, 4000}, {64, 64, 230, 2500}};
 
 // Time until all tiles are done: `big` tiles of cost cb in rounds over the
