@@ -386,7 +386,9 @@ kvc_status kvc_swiglu(const void* gate_up, int64_t n, int64_t inter, void* out, 
  * bf16 [n, k], the weight in the [out, in] layout of a linear layer;
  * residual: device bf16 [m, n] or NULL; c: device bf16 [m, n], which may be
  * the residual buffer itself (added in place) but must not overlap a, w or
- * a_rows.  k: a multiple of 64 in [64, 2^24] (KVC_ERR_UNSUPPORTED
+ * a_rows.  The same call gives the same bits; the order of a row's float32
+ * sums, and with it the last bit of some outputs, depends on the tile the row
+ * falls in: on m, n, k and the row's place in the call, not on the row alone.  k: a multiple of 64 in [64, 2^24] (KVC_ERR_UNSUPPORTED
  * otherwise); n: a multiple of 8 in [0, 2^24]; m <= 2^31 - 128 and about
  * m n <= 2^39 (one launch).  The O and down projections add the residual
  * stream here.

@@ -48,8 +48,8 @@
 //   limit): the queries, the largest position (which every wave finds for
 //   itself) and the first three key tiles are requested without a barrier
 //   between them, and tile 0 is used while tiles 1 and 2 arrive: 1,088 rows
-//   of 8 / 2 heads in eight splits 16.8 -> 14.9 us, 4,096 rows of 32 / 8
-//   heads in three 45.5 -> 43.0 us.
+//   of 8 / 2 heads in eight splits 17.2 -> 14.0 us, 4,096 rows of 32 / 8
+//   heads in three 43.5 -> 40.2 us.
 // - Workgroups run longest query block first, and consecutive workgroup
 //   ids (which the dispatcher spreads over the 8 XCDs) take consecutive kv
 //   heads, so with 8 kv heads each XCD's L2 serves one head's K/V.
@@ -609,8 +609,8 @@ __global__ __launch_bounds__(kThreads) void sparse_attn_kernel(const AttnParams 
 // in split order, so the result is deterministic; a query with no visible key
 // gets 0 and LSE -inf.  Bound by the partials' bytes (516 per query, head and
 // split, all requested before the first is used): 696 rows x 32 heads in
-// three splits took 12 us with a wave per query and head, 7.6 us now, 18,856
-// x 4 in two splits 27 and 15 us.
+// three splits took 12.2 us with a wave per query and head, 8.8 us now, 18,856
+// x 4 in two splits 26.4 and 17.8 us.
 constexpr int kMaxSplit = 8;
 constexpr int kCombineThreads = 256;  // one unit: four waves, 32 channels each
 template <int NS>

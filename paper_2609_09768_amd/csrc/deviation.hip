@@ -365,8 +365,8 @@ __global__ __launch_bounds__(kThreads) void kv_deviation_rows_kernel(const uint1
 // per shift tile (at most 16 rows there), LPR lanes per row, each lane UPL
 // units (8 pairs of one head: 16 bytes of each half), rotated, stored and
 // compared while in registers.  Such a request is bound by launches, not
-// bytes: at 1,024 rows of 2 heads this takes 4.9 us (3.6 + 4.8 apart), at
-// 4,000 of 8 10.1 us (6.0 + 6.8).  The float64 work of both in tiles this
+// bytes: at 1,024 rows of 2 heads this takes 4.9 us (4.0 + 4.7 apart), at
+// 4,000 of 8 10.0 us (5.8 + 6.1, and the gap between two launches).  The float64 work of both in tiles this
 // small costs more than the second pass over the keys from about 40,000 rows
 // x heads on: selection of 4,000 / 6,000 rows of 8 heads 19.0 / 28.5 us
 // against 22 / 26.9 apart, of 8,000 / 12,000 of 4 heads 23.2 / 33.8 against

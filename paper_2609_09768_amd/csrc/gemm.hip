@@ -216,8 +216,8 @@ __device__ __forceinline__ void swap_blocks(uint2& a, uint2& b) {
 // constant.  The L2 takes about one piece of a line per store instruction and
 // row, and every CU stores its tile at once, so stores of 32 bytes of a row (8
 // a lane, 37 instructions each) cost more than the K loop where K is short:
-// 8,192 x 8,192 x 64 46.2 -> 36.9 us, x 512 94 -> 85, 30,000 x 4,096 x 64 86 ->
-// 62, 18,856 x 28,672 x 4,096 3,280 -> 3,185.  (Non-temporal stores, which the
+// 8,192 x 8,192 x 64 46.2 -> 36.7 us, x 512 94 -> 83, 30,000 x 4,096 x 64 86 ->
+// 61, 18,856 x 28,672 x 4,096 3,280 -> 3,185.  (Non-temporal stores, which the
 // L2 does not gather into lines, took four times as long.)
 template <int NT, bool RES, bool ZERO>
 __device__ __forceinline__ void store_wave(const GemmParams& P, long long m, long long n, int lane,
@@ -292,10 +292,11 @@ __device__ __forceinline__ void store_wave(const GemmParams& P, long long m, lon
 // 0.93 us per slice (2 x 1031 MFMA cycles are 0.86 us at 2.4 GHz); with all
 // CUs busy 1.40 us, held by the power limit (1.8 GHz) and the shared caches.
 // Against all waves in step with one barrier per slice: 5,056 x 28,672 x
-// 4,096 1008 -> 879 us (1.35 PFLOP/s), 4,096 x 4,096 x 16,384 1.49 PFLOP/s.
+// 4,096 990 -> 850 us (1.40 PFLOP/s), 4,096 x 4,096 x 16,384 415 -> 357 (1.54).
 // NT = 3 takes 1.10 us per slice, 5 % more per column, and is chosen where its
 // tiles fill the CUs better: 696 x 28,672 x 4,096 (450 tiles in two rounds for
-// 336 in one and a third) 176 -> 154 us, 217 x 37,888 x 3,584 90 -> 81 us.
+// 336 in one and a third) 146 us, 203 with 256 x 256 tiles alone, 217 x 37,888
+// x 3,584 69 and 95.
 // Measured and not taken: four phases per slice of 16 MFMAs (3 % slower),
 // raised wave priority in the MFMA phases (no gain), a third slot for the
 // weights (3 % slower), a K start that differs from workgroup to workgroup
@@ -470,9 +471,9 @@ __device__ __forceinline__ void tile_256(const GemmParams& P, const Lds& S, int 
 // 0.48 us (128) or 0.23 us (64): a 128 tile runs at 73 % and a 64 tile at
 // 38 % of the rate of a 256 tile, bound by the loads (64 and 128 bytes per
 // CU and MFMA cycle).  Against 256 x 256 tiles only: 217 x 3,584 x 18,944
-// 428 -> 72 us, 696 x 4,096 x 4,096 94 -> 30 us, 696 x 4,096 x 14,336 316 ->
-// 107 us, and with both sizes in one launch 5,056 x 4,096 x 14,336 692 ->
-// 450 us.  (128 x 256 tiles, 128 x 64 tiles and four waves with two
+// 362 -> 56 us, 696 x 4,096 x 4,096 94 -> 30 us, 696 x 4,096 x 14,336 281 ->
+// 88 us, and with both sizes in one launch 5,056 x 4,096 x 14,336 675 ->
+// 441 us.  (128 x 256 tiles, 128 x 64 tiles and four waves with two
 // workgroups per CU were slower on most shapes.)
 template <int BT, int WM, int WN, int WK>
 __device__ __forceinline__ void tile_ring(const GemmParams& P, const Lds& L, long long m0, int tn) {

@@ -23,8 +23,8 @@ constexpr T gemm_div_up(T a, T b) { return (a + b - 1) / b; }
 // 8 KB per CU), less what other workgroups' slices hide where K is long: the
 // large tile's is 6.9 us at 4,096 x 16,384 x 128, 7.5 at 8,192 x 8,192 x 1,024
 // and 3.9 at 16,200 x 1,024 x 4,096.  The large tiles' values are those that
-// choose best: with 8,000 and 7,000, right for stores of 32 bytes a row, 106
-// shapes of short K on which the choice differs took 4.5 % more (754 x 25,640 x
+// choose best: with 8,000 and 7,000, right for stores of 32 bytes a row, 101
+// shapes of short K on which the choice differs took 5 % more (754 x 25,640 x
 // 576 37 -> 29 us, 1,281 x 4,096 x 512 16.6 -> 14.8), with 5,000 and 4,500 0.5 %.
 // Of the 1,500 ns that small tiles once had: narrow outputs of many rows and
 // short K took small tiles where large ones are better (42,705 x 256 x 1,024

@@ -137,7 +137,8 @@ size_t attention_ws_bytes(int64_t n_sel, int n_q_heads, int n_kv_heads);
 hipError_t launch_gemm(int64_t m, int64_t n, int64_t k, const uint16_t* a, int64_t n_a_rows,
                        const int32_t* a_rows, const uint16_t* w, const uint16_t* res, uint16_t* c,
                        hipStream_t s);
-// Work-items of that launch (HIP allows fewer than 2^32 per launch).
+// Work-items of a launch of 256 x 256 tiles alone, the choice that has to fit
+// one launch for a shape to be accepted (HIP allows fewer than 2^32 of them).
 int64_t gemm_work_items(int64_t m, int64_t n);
 
 // ---- copies of the transfer stage (stage_copy.hip) -----------------------------

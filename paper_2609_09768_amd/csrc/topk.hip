@@ -296,8 +296,8 @@ __device__ __forceinline__ bool among_first(int c, long long rem, const unsigned
   return (sum_lanes<LANES>(r) < rem) & (c < n);
 }
 
-// One workgroup: 4,000 candidates 22 -> 9 us, 1,024 18 -> 7 us against eight
-// byte passes; bound by the chain of its steps (loads, reduction, histogram,
+// One workgroup: 1,024 candidates 18.2 -> 6.6 us, 4,000 22.0 -> 8.3, 16,384 39.4
+// -> 18.2 against eight byte passes; bound by the chain of its steps (loads, reduction, histogram,
 // scan, rank, scan, store), 1 to 2 us each.
 template <int ITEMS>
 __global__ __launch_bounds__(kSmallThreads) void topk_small(const double* __restrict__ dev, long long n,
@@ -416,9 +416,9 @@ hipError_t launch_small(const double* dev, int64_t n, int64_t k, int64_t n_appen
 // finished reading before it arrived there and which nobody adds into before
 // the next barrier.  Once the rest is decided the other two arrays hold the
 // candidates.  Four barriers (range, two histograms, counts and candidates)
-// where eight byte passes took nine: 32,000 candidates 34 -> 19 us, 124,000
-// 38 -> 22 us, and in a layer the deviation's launch zeroes the state (4.7 us
-// for a launch of its own).
+// where eight byte passes took nine: 32,000 candidates 30.6 -> 15.3 us,
+// 124,000 36.8 -> 22.0, and in a layer the deviation's launch zeroes the state
+// (4 us for a launch of its own).
 constexpr int kFusedMaxBlocks = 128;
 constexpr long long kFusedMaxRows = (long long)kFusedMaxBlocks * kTopkRowsPerBlock;
 constexpr int kFusedWaves = kThreads / 64;
