@@ -107,7 +107,6 @@ struct AttnParams {
   int n_kv_heads;
   int group;      // G = Hq / Hkv
   int n_subs;     // groups of 32 queries
-  int units;      // units of a workgroup, at most its waves
   int n_blocks;   // workgroups' worth of units per kv head
   float scale_log2;  // softmax scale * log2(e)
   uint16_t* out;
@@ -118,6 +117,7 @@ struct AttnParams {
   int n_split;
   float* part_o;    // [n_split][kv head][n_sel x G pairs][D], see first_pair
   float* part_lse;  // [n_split][kv head][n_sel x G pairs]
+  int units;        // units of a workgroup, at most its waves
 };
 
 // Query-head pairs of a kv head before unit u: 32 for a unit, fewer for the
@@ -140,6 +140,9 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
+// UNITS: units of a workgroup, 0 where only P.units says (which costs 0.4 us
+// before the first loads, of the 31 of a check layer of 1,024 rows).
+template <int UNITS>
 __global__ __launch_bounds__(kThreads) void sparse_attn_kernel(const AttnParams P) {
   // one array per slot, so alias analysis can tell a slot being loaded
   // from the slots being read
@@ -163,8 +166,9 @@ __global__ __launch_bounds__(kThreads) void sparse_attn_kernel(const AttnParams 
 
   // this wave's unit and this lane's query (one per lane pair l, l^32); a wave
   // past the workgroup's units has none, like the units past the last group
-  const int unit = P.units * block + wave;  // a launch has fewer than 2^23 blocks
-  const int sub = wave < P.units ? unit / P.group : P.n_subs;
+  const int units = UNITS ? UNITS : P.units;
+  const int unit = units * block + wave;  // a launch has fewer than 2^23 blocks
+  const int sub = UNITS == kWaves || wave < units ? unit / P.group : P.n_subs;
   const int h = g * P.group + unit % P.group;
   const long long qi = 32ll * sub + ql;
   const bool in_range = qi < P.n_sel;
@@ -181,8 +185,8 @@ __global__ __launch_bounds__(kThreads) void sparse_attn_kernel(const AttnParams 
   // barrier before the first loads)
   int pmax = -1;
   {
-    const long long q_first = 32ll * (P.units * block / P.group);
-    const long long q_end = std::min<long long>(32ll * ((P.units * block + P.units - 1) / P.group + 1), P.n_sel);
+    const long long q_first = 32ll * (units * block / P.group);
+    const long long q_end = std::min<long long>(32ll * ((units * block + units - 1) / P.group + 1), P.n_sel);
     for (long long q0 = q_first; q0 < q_end; q0 += 64) {
       if (q0 + lane < q_end) {
         long long pp = P.q_pos[q0 + lane];
@@ -781,8 +785,9 @@ hipError_t launch_attention(const uint16_t* q, int64_t n_q_rows, const int32_t* 
   P.n_blocks = (int)div_up((long long)P.n_subs * P.group, P.units);
   P.part_o = sp > 1 ? static_cast<float*>(ws) : nullptr;
   P.part_lse = sp > 1 ? P.part_o + (size_t)sp * n_sel * n_q_heads * kHeadDim : nullptr;
-  hipLaunchKernelGGL(sparse_attn_kernel, dim3((unsigned)P.n_blocks * (unsigned)n_kv_heads * (unsigned)sp),
-                     dim3(kThreads), 0, s, P);
+  const dim3 grid((unsigned)P.n_blocks * (unsigned)n_kv_heads * (unsigned)sp);
+  if (P.units == kWaves) hipLaunchKernelGGL(sparse_attn_kernel<kWaves>, grid, dim3(kThreads), 0, s, P);
+  else hipLaunchKernelGGL(sparse_attn_kernel<0>, grid, dim3(kThreads), 0, s, P);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess || sp == 1) return e;
   return launch_combine(P, s);
